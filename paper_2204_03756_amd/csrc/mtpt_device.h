@@ -31,6 +31,8 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 namespace mtpt {
 
 // ------------------------------------------------------------------ basics
@@ -328,6 +330,9 @@ __device__ __forceinline__ int small_div(int v, float inv)
 {
     return static_cast<int>((static_cast<float>(v) + 0.5f) * inv);
 }
+
+// predicates of the compare builtins (ordered <= and >=, unsigned <)
+constexpr int kFcmpLe = 5, kFcmpGe = 3, kIcmpUlt = 36;
 
 // Wave64 primitives on DPP lane moves (no LDS round trip).  Every lane of
 // the wave must be active.
@@ -750,6 +755,55 @@ template <> __device__ __forceinline__ float win2_of<float>(const SimArgs& a) { 
 template <typename T> __device__ __forceinline__ T wmargin_of(const SimArgs& a);
 template <> __device__ __forceinline__ double wmargin_of<double>(const SimArgs& a) { return a.wmargind; }
 template <> __device__ __forceinline__ float wmargin_of<float>(const SimArgs& a) { return a.wmarginf; }
+
+// Half width of a row's x-window, sqrt(w2) plus the rounding margin, 0 < w2
+// <= win^2.  The square root may be off by a relative 1e-6 upwards only (a
+// wider window costs candidates, a narrower one would lose pairs): FP32 takes
+// the hardware's (1 ulp, within the margin's 8 ulps of the window), FP64 the
+// hardware FP32 root of w2 / win^2 scaled up by 1e-6 (a ratio too small for
+// FP32 stands for a window far below the margin).
+__device__ __forceinline__ float row_window(const SimArgs& a, float w2)
+{
+    return __builtin_amdgcn_sqrtf(w2) + a.wmarginf;
+}
+__device__ __forceinline__ double row_window(const SimArgs& a, double w2)
+{
+    const float r = __builtin_amdgcn_sqrtf(static_cast<float>(w2 * a.iwin2d)) * 1.000001f;
+    return static_cast<double>(r) * a.win + a.wmargind;
+}
+
+// element of an LDS array at a byte offset
+template <typename V>
+__device__ __forceinline__ V lds_at(const V* base, int off)
+{
+    return *reinterpret_cast<const V*>(reinterpret_cast<const char*>(base) + off);
+}
+
+// Cutoff test of one candidate per lane, as a lane mask in scalar registers.
+// FP64: exact.  FP32: r2 <= psi2_out, and band collects the lanes whose r2
+// lies in the band in which only the FP64 test decides (the caller then
+// repeats its chunk with Metric::inside).
+__device__ __forceinline__ uint64_t within(const SimArgs& a, double r2, uint64_t valid, uint64_t&)
+{
+    return __builtin_amdgcn_fcmp(r2, a.psi2, kFcmpLe) & valid;
+}
+__device__ __forceinline__ uint64_t within(const SimArgs& a, float r2, uint64_t valid, uint64_t& band)
+{
+    const uint64_t in = __builtin_amdgcn_fcmpf(r2, a.psi2_out, kFcmpLe) & valid;
+    band |= __builtin_amdgcn_fcmpf(r2, a.psi2_in, kFcmpGe) & in;
+    return in;
+}
+// 2 w + this lane's bit of the lane mask in: one add with the mask as its
+// carry-in (the compiler takes a select, a shift and an or).  in must come
+// from a scalar instruction (here: the and with the valid mask), which the
+// hardware orders before a vector instruction that reads it.
+__device__ __forceinline__ uint32_t shift_in(uint32_t w, uint64_t in)
+{
+    uint32_t r;
+    uint64_t carry_out;
+    asm("v_addc_co_u32_e64 %0, %1, %2, %2, %3" : "=v"(r), "=s"(carry_out) : "v"(w), "s"(in));
+    return r;
+}
 
 // Per-particle accumulator of the two passes.
 template <int PREC, int NS, bool TRANSFER> struct Acc;
@@ -1307,44 +1361,56 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
                         for (int q = 0; q < 3; ++q) {
                             const T dy = dyv[q] > T(0) ? dyv[q] : T(0);
                             const T w2 = win2_of<T>(a) - dy * dy - dz * dz;
-                            const T w = w2 > T(0) ? static_cast<T>(sqrt(w2)) + wmargin_of<T>(a) : T(0);
+                            const T w = w2 > T(0) ? row_window(a, w2) : T(0);
                             wlo[q] = xi[0] - w;
                             whi[q] = xi[0] + w;
-                            if (!(w2 > T(0)))
-                                ll[q] = 0;
+                            ll[q] = w2 > T(0) ? ll[q] : 0u;
                             lmax = max(lmax, ll[q]);
                         }
                         lmax = wave_max_u32(lmax);
                         const int nsteps = 32 - __builtin_clz(lmax | 1u);
                         // per row, the first slot with x >= wlo and the first with
                         // x > whi, both searched over the whole (x-sorted) row:
-                        // wlo <= whi, so the second is never before the first, and
-                        // the six searches advance together
-                        uint32_t slo[3], nlo[3], shi[3], nhi[3];
+                        // wlo <= whi, so the second is never before the first.
+                        // Powers of two downwards: pl[q] (ph[q]) is the LDS byte
+                        // offset of the last slot known to lie before the result
+                        // (one slot before the row at first); a step tries the
+                        // slot st further on, if the row has it (pe: the row's
+                        // last slot; a slot past it reads the row's end, or for an
+                        // empty row the slot after it, and is not taken).  The six
+                        // searches of a step are free of branches, so their LDS
+                        // reads are in flight together; behind branches each
+                        // waited for its own.
+                        constexpr int kS = static_cast<int>(sizeof(T));
+                        int pl[3], ph[3], pe[3], pc[3];
 #pragma unroll
                         for (int q = 0; q < 3; ++q) {
-                            slo[q] = shi[q] = bb[q];
-                            nlo[q] = nhi[q] = ll[q];
+                            pl[q] = ph[q] = (static_cast<int>(bb[q]) - 1) * kS;
+                            pe[q] = pl[q] + static_cast<int>(ll[q]) * kS;
+                            pc[q] = max(pe[q], pl[q] + kS);
                         }
-                        for (int st = 0; st < nsteps; ++st) {
+                        for (int st = kS << (nsteps - 1); st >= kS; st >>= 1) {
+                            T vl[3], vh[3];
 #pragma unroll
                             for (int q = 0; q < 3; ++q) {
-                                const uint32_t hl = nlo[q] >> 1, ml = slo[q] + hl;
-                                const uint32_t hh = nhi[q] >> 1, mh = shi[q] + hh;
-                                const bool gl = nlo[q] > 0u && lpos[0][ml < CAP ? ml : CAP - 1] < wlo[q];
-                                const bool gh = nhi[q] > 0u && !(lpos[0][mh < CAP ? mh : CAP - 1] > whi[q]);
-                                slo[q] = gl ? ml + 1u : slo[q];
-                                nlo[q] = gl ? nlo[q] - hl - 1u : hl;
-                                shi[q] = gh ? mh + 1u : shi[q];
-                                nhi[q] = gh ? nhi[q] - hh - 1u : hh;
+                                vl[q] = lds_at(lpos[0], min(pl[q] + st, pc[q]));
+                                vh[q] = lds_at(lpos[0], min(ph[q] + st, pc[q]));
+                            }
+#pragma unroll
+                            for (int q = 0; q < 3; ++q) {
+                                const bool gl = (pl[q] + st <= pe[q]) & (vl[q] < wlo[q]);
+                                const bool gh = (ph[q] + st <= pe[q]) & !(vh[q] > whi[q]);
+                                pl[q] = gl ? pl[q] + st : pl[q];
+                                ph[q] = gh ? ph[q] + st : ph[q];
                             }
                         }
                         uint64_t pack = 1ull << 63;
 #pragma unroll
                         for (int q = 0; q < 3; ++q) {
-                            const uint32_t off = slo[q] - bb[q];
-                            bb[q] = slo[q];
-                            ll[q] = shi[q] - slo[q];
+                            const uint32_t slo = static_cast<uint32_t>(pl[q] / kS + 1);
+                            const uint32_t off = slo - bb[q];
+                            bb[q] = slo;
+                            ll[q] = static_cast<uint32_t>(ph[q] - pl[q]) / kS;
                             pack = (off < 1024u && ll[q] < 1024u)
                                        ? pack | (static_cast<uint64_t>(off) << (20 * q)) |
                                              (static_cast<uint64_t>(ll[q]) << (20 * q + 10))
@@ -1372,10 +1438,7 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
                     const uint32_t off = k * kT + (k < e0 ? ob0 : (k < e1 ? ob1 : ob2));
                     return valid ? off : obs;
                 };
-                auto ld = [](const auto* base, uint32_t off) {
-                    return *reinterpret_cast<const std::remove_cv_t<std::remove_reference_t<decltype(*base)>>*>(
-                        reinterpret_cast<const char*>(base) + off);
-                };
+                auto ld = [](const auto* base, uint32_t off) { return lds_at(base, static_cast<int>(off)); };
                 // the recorded neighbours serve the wave when every lane has
                 // them (its row-sum tile was staged) and no lane has more
                 // than 63 candidates (ballots: the wave-wide maximum is needed
@@ -1471,14 +1534,45 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
                     continue;
                 }
                 uint32_t mlo = 0, mhi = 0;
-                // candidates in chunks of 32 (the chunk's mask word is
-                // built without a branch: shifted in, first candidate
-                // highest, then bit-reversed)
+                // Candidates in chunks of 32, one mask word per chunk (shifted in,
+                // first candidate highest, then bit-reversed).  The row-sum
+                // pass's chunk is free of branches: FP32 pairs in the band
+                // around the cutoff (about one in 10^5) are only noted, and a
+                // chunk of a wave that met one is run again with the FP64
+                // test.  The pass is bound by VALU issue on large sims and by
+                // the latency of one wave's chain on small ones; a branch per
+                // candidate kept the LDS reads of successive candidates apart,
+                // each waiting for its own.  With the branch-free window search
+                // and the one-instruction mask bit, against a branch per
+                // candidate and per search step: 2e6-particle 3-d walk 288 ->
+                // 244 us a launch, 3.2e7 reacting 1.48 -> 1.40 ms, 4e6 2-d 92
+                // -> 82 us, 1e5 3-d (one wave per SIMD) 62 -> 45 us.
                 for (uint32_t k0 = 0; k0 < kmax; k0 += 32u) {
                     const uint32_t kend = min(kmax, k0 + 32u);
                     uint32_t mw = 0;
-#pragma unroll kUnroll
-                    for (uint32_t k = k0; k < kend; ++k) {
+                    // candidates k .. k + U - 1, their LDS reads first
+                    auto group = [&](auto width, uint32_t k, uint64_t& band) {
+                        constexpr int U = width;
+                        uint32_t off[U];
+                        T xj[U][3];
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            off[u] = slot_of(k + u, k + u < tot);
+#pragma unroll
+                            for (int d = 0; d < D; ++d)
+                                xj[u][d] = ld(lpos[d], off[u]);
+                        }
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            const T r2 = Metric<D, T, TN>::r2(a, xi, xj[u]);
+                            const uint64_t in =
+                                within(a, r2, __builtin_amdgcn_uicmp(k + u, tot, kIcmpUlt), band);
+                            visit(off[u], __builtin_amdgcn_inverse_ballot_w64(in), r2);
+                            mw = shift_in(mw, in);
+                        }
+                    };
+                    // one candidate, with the exact test
+                    auto single = [&](uint32_t k) {
                         const bool valid = k < tot;
                         const uint32_t off = slot_of(k, valid);
                         T xj[3];
@@ -1490,8 +1584,39 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
                         if (TRANSFER)
                             in = in && off != obs;
                         visit(off, in, r2);
-                        if constexpr (!TRANSFER)
-                            mw = (mw << 1) | (in ? 1u : 0u);
+                        mw = (mw << 1) | (in ? 1u : 0u);
+                    };
+                    if constexpr (TRANSFER || EXPORT) {
+#pragma unroll kUnroll
+                        for (uint32_t k = k0; k < kend; ++k)
+                            single(k);
+                    } else {
+                        constexpr int kGroup = D == 3 ? MTPT_ROW_GROUP_3D
+                                                      : (PREC == 0 ? MTPT_ROW_GROUP_2D_F64 : MTPT_ROW_GROUP_2D);
+                        const auto before = acc;
+                        uint64_t band = 0ull;
+                        uint32_t k = k0;
+                        for (; k + kGroup <= kend; k += kGroup)
+                            group(std::integral_constant<int, kGroup>{}, k, band);
+                        if constexpr (kGroup > 4)
+                            if (k + 4 <= kend) {
+                                group(std::integral_constant<int, 4>{}, k, band);
+                                k += 4;
+                            }
+                        if constexpr (kGroup > 2)
+                            if (k + 2 <= kend) {
+                                group(std::integral_constant<int, 2>{}, k, band);
+                                k += 2;
+                            }
+                        if constexpr (kGroup > 1)
+                            if (k < kend)
+                                group(std::integral_constant<int, 1>{}, k, band);
+                        if (__builtin_expect(band != 0ull, 0)) {
+                            acc = before;
+                            mw = 0;
+                            for (k = k0; k < kend; ++k)
+                                single(k);
+                        }
                     }
                     if constexpr (!TRANSFER) {
                         // candidate k0 + j at bit j

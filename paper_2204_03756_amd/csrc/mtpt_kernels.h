@@ -102,6 +102,20 @@ template <int D, int PREC, int NS> struct LdsBudget {
 #define MTPT_CAND_UNROLL_3D_S3 2
 #endif
 
+// candidates of the row-sum pass's loop whose LDS reads are issued together
+// (measured, us a launch for 1, 2, 3, 4 of the 4e6-particle 2-d pass: 90, 83,
+// 84, 86; for 2, 4, 6, 8 of the 1e5-particle 3-d one: 48, 45, 43, 43, and of
+// the 2e6-particle one: 244, 245, 242, 248)
+#ifndef MTPT_ROW_GROUP_2D
+#define MTPT_ROW_GROUP_2D 2
+#endif
+#ifndef MTPT_ROW_GROUP_2D_F64
+#define MTPT_ROW_GROUP_2D_F64 2
+#endif
+#ifndef MTPT_ROW_GROUP_3D
+#define MTPT_ROW_GROUP_3D 4
+#endif
+
 // Largest tile (cells in x, y and z) of the mass-transfer passes, the halo
 // cell rows it spans and the cell boundaries kept per halo row.  Halo rows
 // (segments) are numbered with a fixed pitch per plane, seg_y (a power of two
@@ -171,6 +185,7 @@ struct SimArgs {
     double win;              // x-window half width, psi (1 + 1e-6)
     double side[3];          // cell side per dimension
     double win2d;            // win * win
+    double iwin2d;           // 1 / win2d
     float win2f;
     float wmarginf;          // rounding margin of row windows (FP32 positions)
     double wmargind;         // the same for FP64 positions

@@ -521,6 +521,7 @@ SimArgs base_args(const mtpt_sim* s)
     a.psi2 = q.psi * q.psi;
     a.win = q.psi * std::sqrt(s->tens.t[0]) * (1.0 + 1e-6);
     a.win2d = a.win * a.win;
+    a.iwin2d = 1.0 / a.win2d;
     a.win2f = static_cast<float>(a.win2d);
     {
         // rounding margin of the per-row windows: 8 ulps of the largest
