@@ -224,11 +224,14 @@ struct SimArgs {
     uint32_t* bsum;
     double* partials;
     uint32_t* pair_part;
+    const double* fin_partials;   // transfer of a static sim: the previous step's partial
+                                  // sums, finalized by this launch (null: none)
     DevStats* st;
     uint32_t scan_blocks;    // ceil((ncells + 1) / kScanTile)
     int32_t scan_fold;       // scan_blocks <= kScanFold: the down pass sums the block totals itself
     uint32_t part_blocks;    // ceil(n / kBlock)
     int32_t recompute_s;     // the row-sum pass ran this step
+    int32_t fin_counted;     // and the step of fin_partials
     int32_t walk;            // apply the jump in the bin pass (0 at create)
     int32_t fuse_bin;        // the transfer pass also bins for the next step
     int32_t tcounts_valid;   // this step's binning came from the transfer pass:

@@ -49,20 +49,20 @@ template <int D, int PREC>
 __global__ __launch_bounds__(kBlock) void place_fin_k(SimArgs a, SimArgs prev)
 {
     if (blockIdx.x == 0) {
-        finalize_body<kBlock>(prev, prev.nttiles, 0);
+        finalize_body<kBlock>(prev, prev.partials, prev.recompute_s != 0, prev.nttiles, 0);
         return;
     }
     place_body<D, typename Types<PREC>::T, typename Types<PREC>::M>(a, xcd_block(blockIdx.x - 1, gridDim.x - 1));
 }
 __global__ __launch_bounds__(kFinalBlock) void finalize_k(SimArgs a, uint32_t nparts, int mode)
 {
-    finalize_body<kFinalBlock>(a, nparts, mode);
+    finalize_body<kFinalBlock>(a, a.partials, a.recompute_s != 0, nparts, mode);
 }
 __global__ __launch_bounds__(kFinalBlock) void finalize_kb(Batch b)
 {
     MTPT_BATCH_PROLOGUE;
     (void)l;
-    finalize_body<kFinalBlock>(a, a.nttiles, 0);
+    finalize_body<kFinalBlock>(a, a.partials, a.recompute_s != 0, a.nttiles, 0);
 }
 
 #undef MTPT_BATCH_PROLOGUE

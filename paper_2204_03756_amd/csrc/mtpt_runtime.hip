@@ -429,6 +429,7 @@ struct mtpt_sim {
     uint64_t* cmask = nullptr;
     uint64_t* cwin = nullptr;
     double* partials = nullptr;
+    double* partials_odd = nullptr;   // static sims: partial sums of odd steps (see carve)
     uint32_t* pair_part = nullptr;
     DevStats* st = nullptr;
     int64_t steps_done = 0;   // steps enqueued since create
@@ -478,6 +479,11 @@ void carve(mtpt_sim* s)
     s->starts = reinterpret_cast<uint32_t*>(b + q.off_starts);
     s->bsum = reinterpret_cast<uint32_t*>(b + q.off_bsum);
     s->partials = reinterpret_cast<double*>(b + q.off_part);
+    // a static sim's transfer launch finalizes the step before it, whose partial
+    // sums then lie apart from the step's own: in the jumps, which a static sim
+    // has no use for (a grid of more tiles than they hold finalizes on its own)
+    if (!s->moving && static_cast<size_t>(q.n) * q.tsz >= static_cast<size_t>(q.nttiles) * q.ns * 8)
+        s->partials_odd = reinterpret_cast<double*>(b + q.off_jmp[0]);
     s->pair_part = reinterpret_cast<uint32_t*>(b + q.off_pair);
     s->st = reinterpret_cast<DevStats*>(b + q.off_stats);
 }
@@ -622,6 +628,8 @@ SimArgs step_args(const mtpt_sim* s, bool* rowsum_needed)
             a.m_dst[c] = s->M[(t + 1) & 1][c];
         }
         a.recompute_s = s->s_valid ? 0 : 1;
+        if ((t & 1) && s->partials_odd)
+            a.partials = s->partials_odd;
     }
     a.fuse_bin = s->moving ? 1 : 0;
     a.tcounts_valid = (s->moving && s->bin_ready) ? 1 : 0;
@@ -686,7 +694,13 @@ int enqueue_step(mtpt_sim* s)
     // the previous step's finalize joins this step's place launch when the
     // step has one (a moving sim whose particles are binned)
     const bool merge = s->fin_pending && s->moving && s->bin_ready;
-    if (s->fin_pending && !merge) {
+    // a static sim's joins the transfer launch
+    const bool merge_static = s->fin_pending && !s->moving && s->partials_odd;
+    if (merge_static) {
+        a.fin_partials = s->fin_args.partials;
+        a.fin_counted = s->fin_args.recompute_s;
+    }
+    if (s->fin_pending && !merge && !merge_static) {
         const int rc = flush_finalize(s);
         if (rc)
             return rc;
@@ -707,6 +721,7 @@ int enqueue_step(mtpt_sim* s)
     if (rc)
         return rc;
     s->fin_args = a;
+    s->fin_args.fin_partials = nullptr;
     s->fin_pending = true;
     s->steps_done += 1;
     if (!s->moving)
