@@ -946,15 +946,10 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
     constexpr int kSegs = TileLimits<D>::segs;
     constexpr int kRows = TileLimits<D>::own_rows;   // own rows (pitch kSY per plane)
     constexpr int kSY = TileLimits<D>::seg_y;
-    __shared__ uint32_t seg_gb[kSegs];
-    __shared__ uint32_t seg_off[kSegs + 1];
+    static_assert(kSegs <= 64, "a lane of a wave stands for each halo row");
+    __shared__ uint32_t rbound[4][kSegs];
     __shared__ uint32_t cst[kSegs][TileLimits<D>::cols];
-    __shared__ uint32_t own_gb[kRows];
-    __shared__ uint32_t own_pre[kRows + 1];
-    // the own-row table in 2-d; in 3-d its bytes would cost both passes a
-    // workgroup per CU, and a search over at most 36 own rows finds the row
-    constexpr bool kRowTab = D == 2 || MTPT_ROW_TABLE_3D != 0;
-    __shared__ uint8_t row_of[kRowTab ? CAP : 1];   // own row of each own particle
+    __shared__ uint32_t seg_gb[EXPORT ? kSegs : 1], seg_off[EXPORT ? kSegs : 1];
     // 2-d FP64 row-sum pass: own cells in order of their candidate count, so
     // that a wave's trip count is near its lanes' mean (the pass's only sum
     // over particles, the pair count, is an integer: the order changes no
@@ -962,6 +957,8 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
     constexpr bool kCellOrder = D == 2 && !TRANSFER && (PREC == 0 ? MTPT_CELL_ORDER_2D : MTPT_CELL_ORDER_2D_F32) != 0;
     constexpr int kCells = kCellOrder ? TileLimits<D>::max_x * TileLimits<D>::max_y : 1;
     __shared__ uint16_t ord[kCellOrder ? CAP : 1];
+    __shared__ uint32_t own_pre[kCellOrder ? kRows : 1];
+    __shared__ uint8_t row_of[kCellOrder ? CAP : 1];   // own row of each own particle
     __shared__ uint8_t ckey[kCells];
     __shared__ uint32_t obase[64];
     // per-cell counts of the particles that stay in the tile, two 16-bit
@@ -1004,119 +1001,151 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
         for (int k = tid; k < (tw * nown + 1) / 2; k += kBlock)
             hist[k] = 0u;
 
-    // every cell boundary of the halo rows in one round of loads, as global
-    // slots (a row outside the grid is empty); the runs of the halo rows and
-    // of the own rows follow from it.  A thread issues all its loads before
-    // its first LDS store, so that they are in flight together (one round
-    // trip instead of one per entry: measured 3.8 -> ~1.5 us of a 3-d tile).
+    // Tile setup, bound by latency: two dependent rounds of global loads (the
+    // cell boundaries of the halo rows, then their particles) and two
+    // barriers.  Every wave works out the halo rows' and own rows' extents
+    // for itself, lane r for row r, and finds the row of a slot by a search
+    // through those lanes (ds_bpermute), so that no scan and no table crosses
+    // waves.  Against block-wide scans (seven barriers) and searches in LDS
+    // tables: 2-d transfer pass 93 -> 89 us (4e6 particles, FP32W) and 46.6 ->
+    // 45.5 us (1e6, FP64), 1000 particles 8.1 -> 7.6 us and their row-sum pass
+    // 7.8 -> 7.2 us, reacting 3-d FP64 (1e6) 108.5 -> 106.5 us, the other 3-d
+    // passes within 1 %.
+    const int lane = tid & 63;
+    auto lane_u32 = [](uint32_t v, int l) {
+        return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), l));
+    };
+    auto from_lane = [](uint32_t v, uint32_t l) {
+        return static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(static_cast<int>(l * 4u), static_cast<int>(v)));
+    };
+    // last row r < n whose start (lane r of start) is <= at[k], for every k at
+    // once: an empty row shares its start with the next one, which then wins
+    auto find_rows = [&](uint32_t start, auto n, const auto& at, auto& row) {
+        constexpr int N = std::extent_v<std::remove_reference_t<decltype(at)>>;
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+            row[k] = 0u;
+#pragma unroll
+        for (int len = n; len > 1;) {
+            const uint32_t half = static_cast<uint32_t>(len >> 1);
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+                row[k] = from_lane(start, row[k] + half) <= at[k] ? row[k] + half : row[k];
+            len -= static_cast<int>(half);
+        }
+    };
+    // Every cell boundary of the halo rows in one round of loads, as global
+    // slots (a row outside the grid is empty).  Thread k of a round takes
+    // boundary c = k % kCP of halo row k / kCP (a power-of-two pitch: no
+    // integer division); the values stay in registers until the rows' LDS
+    // offsets are known.
     const int ncb = ncol + 1;
-    // Thread k of a round takes boundary c = k % kCP of halo row k / kCP (a
-    // power-of-two pitch: no integer division).  The loaded global slots stay
-    // in registers until the rows' LDS offsets are known, then are stored
-    // converted (kept as global slots when the tile does not fit the LDS).
     constexpr int kCP = TileLimits<D>::col_p;
     constexpr int kCstIt = (kSegs * kCP + kBlock - 1) / kBlock;
+    const int cc = tid % kCP;
     uint32_t cv[kCstIt];
 #pragma unroll
     for (int it = 0; it < kCstIt; ++it) {
-        const int idx = tid + it * kBlock;
-        const int sg = idx / kCP;
-        const int c = idx % kCP;
+        const int sg = (tid + it * kBlock) / kCP;
         const int pzr = D == 3 ? sg / kSY : 0;
         const int pyr = D == 3 ? sg % kSY : sg;
         const int pz = z0 - 1 + pzr;
         const int py = y0 - 1 + pyr;
-        const bool in = sg < kSegs && c < ncb && pyr < rows && (D == 2 || pzr < nz + 2) && py >= 0 &&
+        const bool in = sg < kSegs && cc < ncb && pyr < rows && (D == 2 || pzr < nz + 2) && py >= 0 &&
                         py < nc1 && (D == 2 || (pz >= 0 && pz < nc2));
-        cv[it] = in ? a.starts[(static_cast<uint32_t>(D == 3 ? pz : 0) * nc1 + py) * nc0 + xa + c] : 0u;
+        cv[it] = in ? a.starts[(static_cast<uint32_t>(D == 3 ? pz : 0) * nc1 + py) * nc0 + xa + cc] : 0u;
     }
+    // the ends of every halo row and of its own part, for the other waves
+    if (cc == 0 || cc == ncol) {
 #pragma unroll
-    for (int it = 0; it < kCstIt; ++it) {
-        const int idx = tid + it * kBlock;
-        if (idx / kCP < kSegs && idx % kCP < ncb)
-            cst[idx / kCP][idx % kCP] = cv[it];
+        for (int it = 0; it < kCstIt; ++it)
+            if ((tid + it * kBlock) / kCP < kSegs)
+                rbound[cc == 0 ? 0 : 1][(tid + it * kBlock) / kCP] = cv[it];
+    }
+    if (cc == x0 - xa || cc == x1 - xa) {
+#pragma unroll
+        for (int it = 0; it < kCstIt; ++it)
+            if ((tid + it * kBlock) / kCP < kSegs)
+                rbound[cc == x0 - xa ? 2 : 3][(tid + it * kBlock) / kCP] = cv[it];
     }
     __syncthreads();
-    uint32_t slen = 0;
-    if (tid < kSegs) {
-        seg_gb[tid] = cst[tid][0];
-        slen = cst[tid][ncol] - cst[tid][0];
+    // lane r: halo row r, staged at LDS slots s_off .. from sorted slots s_off + s_dd ..;
+    // own row r, own particles o_pre .., their sorted slots o_pre + o_dd ..,
+    // their LDS slots o_pre + o_ld ..
+    uint32_t s_len = 0, s_gb = 0;
+    if (lane < kSegs) {
+        s_gb = rbound[0][lane];
+        s_len = rbound[1][lane] - s_gb;
     }
-    uint32_t total;
-    const uint32_t soff = block_excl_scan(slen, &total);
-    if (tid < kSegs)
-        seg_off[tid] = soff;
-    if (tid == 0)
-        seg_off[kSegs] = total;
-    uint32_t olen = 0;
-    if (tid < kRows) {
-        const int ry = D == 3 ? tid % kSY : tid;
-        const int rz = D == 3 ? tid / kSY : 0;
-        uint32_t gb = 0;
+    const uint32_t s_inc = wave_incl_scan(s_len);
+    const uint32_t s_off = s_inc - s_len;
+    const uint32_t s_dd = s_gb - s_off;
+    const uint32_t total = lane_u32(s_inc, 63);
+    uint32_t o_len = 0, o_gb = 0;
+    const int o_seg = srow(lane < kRows ? lane : 0);
+    if (lane < kRows) {
+        const int ry = D == 3 ? lane % kSY : lane;
+        const int rz = D == 3 ? lane / kSY : 0;
         if (ry < nrow && rz < nz) {
-            const int sr = srow(tid);
-            gb = cst[sr][x0 - xa];
-            olen = cst[sr][x1 - xa] - gb;
+            o_gb = rbound[2][o_seg];
+            o_len = rbound[3][o_seg] - o_gb;
         }
-        own_gb[tid] = gb;
     }
-    uint32_t own_total;
-    const uint32_t ooff = block_excl_scan(olen, &own_total);
-    if (tid < kRows)
-        own_pre[tid] = ooff;
-    if (tid == 0)
-        own_pre[kRows] = own_total;
-    __syncthreads();
+    const uint32_t o_inc = wave_incl_scan(o_len);
+    const uint32_t o_pre = o_inc - o_len;
+    const uint32_t o_dd = o_gb - o_pre;
+    const uint32_t o_ld = o_dd - from_lane(s_dd, static_cast<uint32_t>(o_seg));
+    const uint32_t own_total = lane_u32(o_inc, 63);
+    if constexpr (EXPORT) {
+        if (tid < kSegs) {
+            seg_gb[tid] = s_gb;
+            seg_off[tid] = s_off;
+        }
+    }
 
     const bool use_lds = total <= static_cast<uint32_t>(CAP);
-    // cell boundaries of every halo row as LDS offsets (read by the particle
-    // loop after the staging barrier)
-    if (use_lds) {
+    // cell boundaries of every halo row as LDS offsets, or as sorted slots
+    // when the tile does not fit the LDS (read by the particle loop after the
+    // staging barrier)
 #pragma unroll
-        for (int it = 0; it < kCstIt; ++it) {
-            const int idx = tid + it * kBlock;
-            const int sg = idx / kCP;
-            if (sg < kSegs && idx % kCP < ncb)
-                cst[sg][idx % kCP] = cv[it] - seg_gb[sg] + seg_off[sg];
-        }
+    for (int it = 0; it < kCstIt; ++it) {
+        const int sg = (tid + it * kBlock) / kCP;
+        const uint32_t dd = from_lane(s_dd, static_cast<uint32_t>(sg & 63));
+        if (sg < kSegs && cc < ncb)
+            cst[sg][cc] = use_lds ? cv[it] - dd : cv[it];
     }
-    // own row of every own particle, when they fit the table (2-d)
-    const bool rows_tab = kRowTab && own_total <= static_cast<uint32_t>(CAP);
-    if (rows_tab)
-        for (int r = tid >> 6; r < kRows; r += kBlock / 64)
-            for (uint32_t j = static_cast<uint32_t>(tid & 63); j < own_pre[r + 1] - own_pre[r]; j += 64)
-                row_of[own_pre[r] + j] = static_cast<uint8_t>(r);
+    // own row of every own particle, when they fit the table
+    const bool rows_tab = kCellOrder && own_total <= static_cast<uint32_t>(CAP);
+    if constexpr (kCellOrder) {
+        if (tid < kRows)
+            own_pre[tid] = o_pre;
+        if (rows_tab)
+            for (int r = __builtin_amdgcn_readfirstlane(tid >> 6); r < kRows; r += kBlock / 64)
+                for (uint32_t j = static_cast<uint32_t>(lane); j < lane_u32(o_len, r); j += 64)
+                    row_of[lane_u32(o_pre, r) + j] = static_cast<uint8_t>(r);
+    }
     if (use_lds) {
         // Each halo row is one contiguous run in HBM and in LDS.  A thread
         // stages slots tid, tid + kBlock, ...: it finds every slot's row
         // first (the searches advance together), then issues all its loads,
         // then all its LDS stores, so that its loads are in flight at once.
         constexpr int kIt = (CAP + kBlock - 1) / kBlock;
-        uint32_t sidx[kIt];
-        int sb[kIt];
-#pragma unroll
-        for (int it = 0; it < kIt; ++it) {
-            sidx[it] = static_cast<uint32_t>(tid + it * kBlock);
-            sb[it] = 0;
-        }
-        // last row whose first slot is <= the slot (seg_off[0] = 0; an empty
-        // row shares its offset with the next one, which then wins); the range
-        // [sb, sb + len) always holds it
-#pragma unroll
-        for (int len = kSegs; len > 1;) {
-            const int half = len >> 1;
-#pragma unroll
-            for (int it = 0; it < kIt; ++it)
-                sb[it] = seg_off[sb[it] + half] <= sidx[it] ? sb[it] + half : sb[it];
-            len -= half;
-        }
         T vx[kIt][D];
         T vs[kIt];
         M vm[kIt][NS];
+        uint32_t slots[kIt], sdd[kIt];
+#pragma unroll
+        for (int it = 0; it < kIt; ++it)
+            slots[it] = static_cast<uint32_t>(tid + it * kBlock);
+        find_rows(s_off, std::integral_constant<int, kSegs>{}, slots, sdd);
+#pragma unroll
+        for (int it = 0; it < kIt; ++it)
+            sdd[it] = from_lane(s_dd, sdd[it]);
 #pragma unroll
         for (int it = 0; it < kIt; ++it) {
-            if (sidx[it] < total) {
-                const uint32_t g = seg_gb[sb[it]] + (sidx[it] - seg_off[sb[it]]);
+            const uint32_t slot = static_cast<uint32_t>(tid + it * kBlock);
+            if (slot < total) {
+                const uint32_t g = slot + sdd[it];
 #pragma unroll
                 for (int d = 0; d < D; ++d)
                     vx[it][d] = static_cast<const T*>(a.x[d])[g];
@@ -1130,8 +1159,8 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
         }
 #pragma unroll
         for (int it = 0; it < kIt; ++it) {
-            if (sidx[it] < total) {
-                const uint32_t idx = sidx[it];
+            const uint32_t idx = static_cast<uint32_t>(tid + it * kBlock);
+            if (idx < total) {
 #pragma unroll
                 for (int d = 0; d < D; ++d)
                     lpos[d][idx] = vx[it][d];
@@ -1203,31 +1232,23 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
         const uint32_t t = base + tid;
         const bool act = t < own_total;
         uint32_t tt = act ? t : own_total - 1u;
-        if constexpr (kCellOrder) {
-            if (cell_order)
-                tt = ord[tt];
-        }
-        int r = 0;
-        if (rows_tab) {
-            r = row_of[kRowTab ? tt : 0u];
+        int r;
+        if (cell_order) {
+            tt = ord[kCellOrder ? tt : 0u];
+            r = row_of[kCellOrder ? tt : 0u];
         } else {
-            // last own row whose first particle is <= tt (an empty row shares
-            // its offset with the next one, which then wins), in fixed steps
-#pragma unroll
-            for (int len = kRows; len > 1;) {
-                const int half = len >> 1;
-                r = own_pre[r + half] <= tt ? r + half : r;
-                len -= half;
-            }
+            const uint32_t at[1] = {tt};
+            uint32_t row[1];
+            find_rows(o_pre, std::integral_constant<int, kRows>{}, at, row);
+            r = static_cast<int>(row[0]);
         }
-        const uint32_t i = own_gb[r] + (tt - own_pre[r]);
-        // the particle's LDS slot; its own position (and, in the transfer
-        // pass, row sum and masses) from there when the tile is staged, else
-        // coalesced global loads (LDS reads and global loads stay separate
-        // instructions: a select of the two addresses would make them flat
-        // loads)
-        const int smid0 = srow(r);
-        const uint32_t lself = i - seg_gb[smid0] + seg_off[smid0];
+        // the particle's sorted slot and its LDS slot; its own position (and,
+        // in the transfer pass, row sum and masses) from there when the tile
+        // is staged, else coalesced global loads (LDS reads and global loads
+        // stay separate instructions: a select of the two addresses would
+        // make them flat loads)
+        const uint32_t i = tt + from_lane(o_dd, static_cast<uint32_t>(r));
+        const uint32_t lself = tt + from_lane(o_ld, static_cast<uint32_t>(r));
         const uint32_t lq = use_lds ? lself : 0u;
         // first halo row of the particle's lowest candidate plane
         const int rbase = r;

@@ -74,10 +74,6 @@ template <int D, int PREC, int NS> struct LdsBudget {
         D == 3 ? (PREC != 0 ? (NS == 1 ? MTPT_LDS_BUDGET_3D : MTPT_LDS_BUDGET_3D_S3) : MTPT_LDS_BUDGET_3D_WIDE)
                : (PREC == 0 ? MTPT_LDS_BUDGET_2D_F64 : MTPT_LDS_BUDGET_2D);
 };
-// 3-d tiled passes keep a table of each own particle's row (else a search)
-#ifndef MTPT_ROW_TABLE_3D
-#define MTPT_ROW_TABLE_3D 0
-#endif
 // the 2-d FP64 row-sum pass hands its own cells to lanes in order of their
 // candidate count
 #ifndef MTPT_CELL_ORDER_2D
