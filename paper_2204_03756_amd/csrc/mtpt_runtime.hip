@@ -306,6 +306,16 @@ Plan make_plan(const mtpt_params& p)
 #ifndef MTPT_TILE_OWN
 #define MTPT_TILE_OWN 640.0
 #endif
+// Tiles below which (eight per compute unit) a 3-d tile's own particles are
+// counted in whole workgroups of lanes instead of waves: with so few tiles the
+// launch lasts as long as its slowest workgroup, and a second pass over the
+// particles that holds a few waves doubles that (measured, us a step with
+// waves / with workgroups: 1e5-particle walk Kahan 92 / 77, reacting 1e5 FP64
+// 75 / 69, 6e4 FP32W 52 / 48.6, 4e5 93 / 87; 3e5 Kahan 120.6 / 122).  At 4096
+// the reacting 1e6 FP64 step lost 4 %, at 1024 the 3e5 ones 7-10 %.
+#ifndef MTPT_LAT_TILES
+#define MTPT_LAT_TILES 2048
+#endif
 #ifndef MTPT_TILE_LANES
 #define MTPT_TILE_LANES 64.0
 #endif
@@ -335,8 +345,9 @@ Plan make_plan(const mtpt_params& p)
                             if ((halo > cap || tiles_of(x, y, z) < min_tiles) && !unit)
                                 continue;
                             const double own = std::max(1e-9, x * y * static_cast<double>(z) * rho_c);
-                            const double passes = std::ceil((own + 2.0 * std::sqrt(own)) / MTPT_TILE_LANES);
-                            const double cost = (passes * MTPT_TILE_LANES + 0.02 * halo + 25.0) / own;
+                            const double lanes = tiles_of(x, y, z) < MTPT_LAT_TILES ? static_cast<double>(kBlock) : MTPT_TILE_LANES;
+                            const double passes = std::ceil((own + 2.0 * std::sqrt(own)) / lanes);
+                            const double cost = (passes * lanes + 0.02 * halo + 25.0) / own;
                             if (best == 0.0 || cost < best) {
                                 best = cost;
                                 tx = x;
