@@ -237,7 +237,8 @@ int mtpt_phase_times(mtpt_sim* sim, const char** names, double* ms, int64_t* lau
 
 /* hbm_budget: bytes of device memory the pool may hold (0: 90 % of free
  * memory at create).  max_slots: most sims active at once (>= 1, else
- * MTPT_E_ARG).  hip_stream and alloc as for mtpt_create. */
+ * MTPT_E_ARG).  hip_stream and alloc as for mtpt_create; with NULL the pool
+ * has two streams of its own and steps its 2-d and its 3-d sims side by side. */
 int mtpt_pool_create(size_t hbm_budget, int32_t max_slots, void* hip_stream,
                      const mtpt_allocator* alloc, mtpt_pool** out);
 

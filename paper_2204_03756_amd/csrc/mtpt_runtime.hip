@@ -1405,14 +1405,22 @@ int mtpt_phase_times(mtpt_sim* s, const char** names, double* ms, int64_t* launc
 // search in a prefix of blocks per sim.  The per-tick argument arrays travel
 // through a ring of pinned host buffers and device buffers; a ring slot is
 // reused only after the event recorded behind its last launch has fired.
+//
+// A pool on a stream of its own runs its 2-d and its 3-d sims in two lanes, a
+// stream each: the lanes share nothing but the chip, and where a lane's launch
+// does not fill it (small sims, the last workgroups of every launch) the
+// other's runs beside it (16 sims of 1e4 to 1e6 particles: 86.0 -> 81.8 ms).
+// A pool on the caller's stream keeps to that stream.
 namespace {
+
+constexpr int kLanes = 2;
 
 struct RingSlot {
     void* host = nullptr;    // pinned
     void* dev = nullptr;
     size_t cap = 0;
-    hipEvent_t ev = nullptr;
-    bool armed = false;
+    hipEvent_t ev[kLanes] = {};
+    bool armed[kLanes] = {};
 };
 
 }  // namespace
@@ -1423,6 +1431,7 @@ struct mtpt_pool {
     int32_t max_slots = 1;
     hipStream_t stream = nullptr;
     bool own_stream = false;
+    hipStream_t stream3 = nullptr;       // lane of the 3-d sims; null: the one stream
     Alloc alloc;
     std::map<int64_t, mtpt_sim*> sims;   // ticket -> sim, ordered by admission
     std::map<int64_t, size_t> bytes_of;
@@ -1437,12 +1446,14 @@ namespace {
 
 int ring_reserve(mtpt_pool* p, RingSlot& r, size_t bytes)
 {
-    if (r.armed) {
-        HIP_TRY(hipEventSynchronize(r.ev));
-        r.armed = false;
+    for (int l = 0; l < kLanes; ++l) {
+        if (r.armed[l]) {
+            HIP_TRY(hipEventSynchronize(r.ev[l]));
+            r.armed[l] = false;
+        }
+        if (!r.ev[l])
+            HIP_TRY(hipEventCreateWithFlags(&r.ev[l], hipEventDisableTiming));
     }
-    if (!r.ev)
-        HIP_TRY(hipEventCreateWithFlags(&r.ev, hipEventDisableTiming));
     if (r.cap >= bytes)
         return MTPT_OK;
     if (r.host)
@@ -1520,6 +1531,9 @@ int on_export_stream(mtpt_pool* p, mtpt_sim* s, F fn)
     return rc;
 }
 
+// stream that the pool's sims of this dimension run on
+hipStream_t lane_stream(const mtpt_pool* p, int dim) { return dim == 3 && p->stream3 ? p->stream3 : p->stream; }
+
 struct GroupKey {
     int dim, prec, ns, tensor, moving, rowsum, bin;
     bool operator<(const GroupKey& o) const
@@ -1572,7 +1586,10 @@ int mtpt_pool_create(size_t hbm_budget, int32_t max_slots, void* hip_stream, con
         }
         p->own_stream = true;
     }
-    if (hipStreamCreateWithFlags(&p->xstream, hipStreamNonBlocking) != hipSuccess) {
+    if (hipStreamCreateWithFlags(&p->xstream, hipStreamNonBlocking) != hipSuccess ||
+        (p->own_stream && hipStreamCreateWithFlags(&p->stream3, hipStreamNonBlocking) != hipSuccess)) {
+        if (p->xstream)
+            (void)hipStreamDestroy(p->xstream);
         if (p->own_stream)
             (void)hipStreamDestroy(p->stream);
         delete p;
@@ -1607,7 +1624,7 @@ int mtpt_pool_admit(mtpt_pool* p, const mtpt_params* params, const double* pos, 
     if (rc)
         return rc;
     mtpt_sim* s = nullptr;
-    rc = new_sim(params, pos, mass, p->stream, p->alloc.custom ? &p->alloc.a : nullptr, &s, stage);
+    rc = new_sim(params, pos, mass, lane_stream(p, params->dim), p->alloc.custom ? &p->alloc.a : nullptr, &s, stage);
     if (rc)
         return rc;
     s->steps_target = n_steps;
@@ -1666,10 +1683,28 @@ int mtpt_pool_tick(mtpt_pool* p, int32_t* n_completed)
             }
             ++gi;
         }
-        HIP_TRY(hipMemcpyAsync(r.dev, r.host, bytes, hipMemcpyHostToDevice, p->stream));
+        // each lane uploads the arguments of its own groups (ordered by
+        // dimension) and records an event behind its last launch
         gi = 0;
+        hipStream_t lane = nullptr;
         for (auto& g : groups) {
             const GroupKey& k = g.first;
+            if (!lane || lane != lane_stream(p, k.dim)) {
+                if (lane) {
+                    HIP_TRY(hipEventRecord(r.ev[0], lane));
+                    r.armed[0] = true;
+                }
+                lane = lane_stream(p, k.dim);
+                size_t end = bytes;
+                size_t gj = gi;
+                for (auto it = groups.find(k); it != groups.end(); ++it, ++gj)
+                    if (lane_stream(p, it->first.dim) != lane) {
+                        end = goff[gj];
+                        break;
+                    }
+                HIP_TRY(hipMemcpyAsync(static_cast<char*>(r.dev) + goff[gi], h + goff[gi], end - goff[gi],
+                                       hipMemcpyHostToDevice, lane));
+            }
             const size_t ns = g.second.size();
             char* d = static_cast<char*>(r.dev);
             const SimArgs* dargs = reinterpret_cast<const SimArgs*>(d + goff[gi]);
@@ -1696,7 +1731,7 @@ int mtpt_pool_tick(mtpt_pool* p, int32_t* n_completed)
                 b.blk_off = dpre + ph * (ns + 1);
                 b.nsims = static_cast<int32_t>(ns);
                 b.total_blocks = hpre[ph * (ns + 1) + ns];
-                HIP_TRY(launch_phase_batched(ph, k.dim, k.prec, k.ns, k.tensor, b, p->stream));
+                HIP_TRY(launch_phase_batched(ph, k.dim, k.prec, k.ns, k.tensor, b, lane));
             }
             for (mtpt_sim* s : g.second) {
                 s->steps_done += 1;
@@ -1709,13 +1744,13 @@ int mtpt_pool_tick(mtpt_pool* p, int32_t* n_completed)
                     // done() and the exports wait for this event only
                     if (!s->done_ev)
                         HIP_TRY(hipEventCreateWithFlags(&s->done_ev, hipEventDisableTiming));
-                    HIP_TRY(hipEventRecord(s->done_ev, p->stream));
+                    HIP_TRY(hipEventRecord(s->done_ev, lane));
                 }
             }
             ++gi;
         }
-        HIP_TRY(hipEventRecord(r.ev, p->stream));
-        r.armed = true;
+        HIP_TRY(hipEventRecord(r.ev[1], lane));
+        r.armed[1] = true;
         p->ticks += 1;
     }
     if (n_completed)
@@ -1734,7 +1769,7 @@ int mtpt_pool_done(mtpt_pool* p, int64_t ticket, int32_t* done)
     *done = 0;
     if (s->steps_done >= s->steps_target) {
         if (!s->done_ev) {
-            HIP_TRY(hipStreamSynchronize(p->stream));
+            HIP_TRY(hipStreamSynchronize(s->stream));
             *done = 1;
             return MTPT_OK;
         }
@@ -1777,7 +1812,7 @@ int mtpt_pool_result(mtpt_pool* p, int64_t ticket, double* mass_out)
     if (rc && rc != MTPT_E_NONFINITE)
         return rc;
     if (!s->done_ev)
-        (void)hipStreamSynchronize(p->stream);
+        (void)hipStreamSynchronize(s->stream);
     release(s);
     p->held -= p->bytes_of[ticket];
     p->bytes_of.erase(ticket);
@@ -1803,6 +1838,8 @@ int mtpt_pool_destroy(mtpt_pool* p)
     if (!p)
         return MTPT_OK;
     (void)hipStreamSynchronize(p->stream);
+    if (p->stream3)
+        (void)hipStreamSynchronize(p->stream3);
     if (p->xstream)
         (void)hipStreamSynchronize(p->xstream);
     for (auto& kv : p->sims)
@@ -1821,9 +1858,12 @@ int mtpt_pool_destroy(mtpt_pool* p)
         if (r.host)
             (void)hipHostFree(r.host);
         p->alloc.put(r.dev);
-        if (r.ev)
-            (void)hipEventDestroy(r.ev);
+        for (hipEvent_t e : r.ev)
+            if (e)
+                (void)hipEventDestroy(e);
     }
+    if (p->stream3)
+        (void)hipStreamDestroy(p->stream3);
     if (p->own_stream && p->stream)
         (void)hipStreamDestroy(p->stream);
     delete p;
