@@ -11,15 +11,21 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
+#include <condition_variable>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <deque>
+#include <limits>
 #include <map>
+#include <memory>
 #include <mutex>
+#include <new>
 #include <string>
+#include <thread>
 #include <vector>
 
 using namespace mtpt;
@@ -45,6 +51,35 @@ int fail(int code, const char* fmt, ...)
         if (e_ != hipSuccess)                                                                      \
             return fail(MTPT_E_DEVICE, "%s failed: %s", #expr, hipGetErrorString(e_));             \
     } while (0)
+
+// Host threads of a large conversion or copy (memory-bound: a few saturate it).
+constexpr int kHostThreads = 8;
+
+// f(begin, end) over [0, n) in one range per thread, at least grain items
+// each, on this thread alone when that is one range.  A thread that cannot be
+// started runs its range here.  f must not throw.
+template <typename F>
+void parallel_ranges(int64_t n, int64_t grain, F f)
+{
+    const int64_t cpus = static_cast<int64_t>(std::max(1u, std::thread::hardware_concurrency()));
+    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>({kHostThreads, cpus, n / grain}));
+    std::thread th[kHostThreads];
+    for (int64_t t = 1; t < parts; ++t) {
+        const int64_t b = n * t / parts, e = n * (t + 1) / parts;
+        try {
+            th[t] = std::thread([&f, b, e] { f(b, e); });
+        } catch (...) {
+            f(b, e);
+        }
+    }
+    f(0, parts > 1 ? n / parts : n);
+    for (auto& x : th)
+        if (x.joinable())
+            x.join();
+}
+// particles per thread below which a thread costs more than it saves (about
+// 30 us to start one, 2.4 ns to check and convert a particle)
+constexpr int64_t kHostGrain = 65536;
 
 struct Alloc {
     mtpt_allocator a{};
@@ -742,6 +777,117 @@ int enqueue_step(mtpt_sim* s)
     return MTPT_OK;
 }
 
+// Copies bytes of device memory to pageable host memory behind the work on
+// the sim's stream, and waits.  A large copy goes through a ring of pinned
+// chunks: this thread keeps the ring's copies in flight and makes every HIP
+// call, and a few others write the chunks that have landed to the caller's
+// pages, first touches included.  One hipMemcpy stages through one thread
+// (768 MB into fresh pages 81 ms against 24 ms); below kCopyThreaded
+// allocating the ring costs more than that saves.
+constexpr size_t kCopyChunk = static_cast<size_t>(4) << 20;
+constexpr size_t kCopyThreaded = static_cast<size_t>(64) << 20;
+constexpr int kCopyRing = 8;
+
+hipError_t copy_out(mtpt_sim* s, void* out, const void* dev, size_t bytes)
+{
+    char* pinned = nullptr;
+    if (bytes >= kCopyThreaded &&
+        hipHostMalloc(reinterpret_cast<void**>(&pinned), kCopyRing * kCopyChunk, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        pinned = nullptr;
+    }
+    if (!pinned) {
+        const hipError_t e = hipMemcpyAsync(out, dev, bytes, hipMemcpyDeviceToHost, s->stream);
+        return e != hipSuccess ? e : hipStreamSynchronize(s->stream);
+    }
+    const int64_t chunks = static_cast<int64_t>((bytes + kCopyChunk - 1) / kCopyChunk);
+    auto length = [&](int64_t c) { return std::min(kCopyChunk, bytes - static_cast<size_t>(c) * kCopyChunk); };
+    // chunk c lands in slot c % kCopyRing; the writers take landed chunks in
+    // order, and a slot is filled again once its chunk is written
+    std::mutex mu;
+    std::condition_variable cv;
+    int64_t landed = 0, taken = 0;
+    int64_t written[kCopyRing];              // last chunk written from each slot
+    bool stop = false;
+    for (int k = 0; k < kCopyRing; ++k)
+        written[k] = k - kCopyRing;
+    auto write = [&](int64_t c) {
+        std::memcpy(static_cast<char*>(out) + static_cast<size_t>(c) * kCopyChunk,
+                    pinned + static_cast<size_t>(c % kCopyRing) * kCopyChunk, length(c));
+    };
+    auto writer = [&] {
+        std::unique_lock<std::mutex> lk(mu);
+        for (;;) {
+            cv.wait(lk, [&] { return stop || taken < landed; });
+            if (taken >= landed)
+                return;
+            const int64_t c = taken++;
+            lk.unlock();
+            write(c);
+            lk.lock();
+            written[c % kCopyRing] = c;
+            cv.notify_all();
+        }
+    };
+    std::thread th[kHostThreads];
+    int writers = 0;
+    for (; writers < kHostThreads; ++writers) {
+        try {
+            th[writers] = std::thread(writer);
+        } catch (...) {
+            break;
+        }
+    }
+    hipEvent_t ev[kCopyRing] = {};
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < kCopyRing && e == hipSuccess; ++k)
+        e = hipEventCreateWithFlags(&ev[k], hipEventDisableTiming);
+    int64_t issued = 0;
+    for (int64_t c = 0; c < chunks && e == hipSuccess; ++c) {
+        // keep the ring full, without waiting for more than chunk c needs
+        for (; issued < chunks && e == hipSuccess; ++issued) {
+            const int k = static_cast<int>(issued % kCopyRing);
+            {
+                std::unique_lock<std::mutex> lk(mu);
+                if (issued == c)
+                    cv.wait(lk, [&] { return written[k] == issued - kCopyRing; });
+                else if (written[k] != issued - kCopyRing)
+                    break;
+            }
+            e = hipMemcpyAsync(pinned + static_cast<size_t>(k) * kCopyChunk,
+                               static_cast<const char*>(dev) + static_cast<size_t>(issued) * kCopyChunk, length(issued),
+                               hipMemcpyDeviceToHost, s->stream);
+            if (e == hipSuccess)
+                e = hipEventRecord(ev[k], s->stream);
+        }
+        if (e == hipSuccess)
+            e = hipEventSynchronize(ev[c % kCopyRing]);
+        if (e != hipSuccess)
+            break;
+        std::unique_lock<std::mutex> lk(mu);
+        landed = c + 1;
+        if (writers == 0) {
+            write(c);
+            taken = landed;
+            written[c % kCopyRing] = c;
+        }
+        cv.notify_all();
+    }
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        stop = true;
+        cv.notify_all();
+    }
+    for (int k = 0; k < writers; ++k)
+        th[k].join();
+    const hipError_t es = hipStreamSynchronize(s->stream);
+    for (hipEvent_t v : ev)
+        if (v)
+            (void)hipEventDestroy(v);
+    (void)hipHostFree(pinned);
+    return e != hipSuccess ? e : es;
+}
+
 int sync(mtpt_sim* s)
 {
     const int rc = flush_finalize(s);
@@ -808,54 +954,60 @@ int create_into(mtpt_sim* s, const double* pos, const double* mass, PinnedStage*
     HIP_TRY(hipMemsetAsync(s->counts, 0, static_cast<size_t>(q.scan_blocks) * kScanTile * 4, s->stream));
     HIP_TRY(hipMemsetAsync(s->tcounts, 0, static_cast<size_t>(q.scan_blocks) * kScanTile * 4, s->stream));
     if (n > 0) {
-        std::vector<unsigned char> pageable;
+        std::unique_ptr<unsigned char[]> pageable;
         unsigned char* stage = nullptr;
         if (st) {
             stage = static_cast<unsigned char*>(st->host);
         } else {
-            pageable.resize(std::max(n * q.tsz, n * q.msz));
-            stage = pageable.data();
+            pageable.reset(new (std::nothrow) unsigned char[std::max(n * q.tsz, n * q.msz)]);
+            stage = pageable.get();
+            if (!stage)
+                return fail(MTPT_E_NOMEM, "host staging allocation failed");
         }
-        // the pinned staging holds every array at once: [dim][n] positions, then
-        // [ns][n] masses; the pageable one one array at a time
-        size_t off = 0;
-        auto upload = [&](void* dst, size_t bytes, const unsigned char* src) -> hipError_t {
-            return st ? hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s->stream)
-                      : hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice);
+        // coordinate k of particles [b, e), rounded once to the position type
+        auto put_pos = [&](unsigned char* h, int k, int64_t b, int64_t e) {
+            if (q.tsz == 8)
+                for (int64_t i = b; i < e; ++i)
+                    reinterpret_cast<double*>(h)[i] = pos[i * q.dim + k];
+            else
+                for (int64_t i = b; i < e; ++i)
+                    reinterpret_cast<float*>(h)[i] = static_cast<float>(pos[i * q.dim + k]);
         };
-        for (int k = 0; k < q.dim; ++k) {
-            // coordinate k, rounded once to the position type
-            unsigned char* h = stage + off;
-            if (q.tsz == 8) {
-                double* d = reinterpret_cast<double*>(h);
-                for (size_t i = 0; i < n; ++i)
-                    d[i] = pos[i * q.dim + k];
-            } else {
-                float* f = reinterpret_cast<float*>(h);
-                for (size_t i = 0; i < n; ++i)
-                    f[i] = static_cast<float>(pos[i * q.dim + k]);
+        auto put_mass = [&](unsigned char* h, int c, int64_t b, int64_t e) {
+            if (q.msz == 8)
+                std::memcpy(h + b * 8, mass + c * n + b, static_cast<size_t>(e - b) * 8);
+            else
+                for (int64_t i = b; i < e; ++i)
+                    reinterpret_cast<float*>(h)[i] = static_cast<float>(mass[c * n + i]);
+        };
+        if (st) {
+            // the pinned staging holds every array at once: [dim][n]
+            // positions, then [ns][n] masses
+            unsigned char* const hm = stage + q.dim * n * q.tsz;
+            parallel_ranges(q.n, kHostGrain, [&](int64_t b, int64_t e) {
+                for (int k = 0; k < q.dim; ++k)
+                    put_pos(stage + k * n * q.tsz, k, b, e);
+                for (int c = 0; c < q.ns; ++c)
+                    put_mass(hm + c * n * q.msz, c, b, e);
+            });
+            for (int k = 0; k < q.dim; ++k)
+                HIP_TRY(hipMemcpyAsync(s->X[k], stage + k * n * q.tsz, n * q.tsz, hipMemcpyHostToDevice, s->stream));
+            for (int c = 0; c < q.ns; ++c)
+                HIP_TRY(hipMemcpyAsync(s->M[1][c], hm + c * n * q.msz, n * q.msz, hipMemcpyHostToDevice, s->stream));
+        } else {
+            // the pageable one holds one array at a time (its copy blocks)
+            for (int k = 0; k < q.dim; ++k) {
+                parallel_ranges(q.n, kHostGrain, [&](int64_t b, int64_t e) { put_pos(stage, k, b, e); });
+                HIP_TRY(hipMemcpy(s->X[k], stage, n * q.tsz, hipMemcpyHostToDevice));
             }
-            HIP_TRY(upload(s->X[k], n * q.tsz, h));
-            if (st)
-                off += n * q.tsz;
-        }
-        for (int c = 0; c < q.ns; ++c) {
-            unsigned char* h = stage + off;
-            if (q.msz == 8) {
-                if (st) {
-                    std::memcpy(h, mass + c * n, n * 8);
-                    HIP_TRY(upload(s->M[1][c], n * 8, h));
-                } else {
-                    HIP_TRY(hipMemcpy(s->M[1][c], mass + c * n, n * 8, hipMemcpyHostToDevice));
+            for (int c = 0; c < q.ns; ++c) {
+                const void* src = mass + c * n;
+                if (q.msz == 4) {
+                    parallel_ranges(q.n, kHostGrain, [&](int64_t b, int64_t e) { put_mass(stage, c, b, e); });
+                    src = stage;
                 }
-            } else {
-                float* f = reinterpret_cast<float*>(h);
-                for (size_t i = 0; i < n; ++i)
-                    f[i] = static_cast<float>(mass[c * n + i]);
-                HIP_TRY(upload(s->M[1][c], n * 4, h));
+                HIP_TRY(hipMemcpy(s->M[1][c], src, n * q.msz, hipMemcpyHostToDevice));
             }
-            if (st)
-                off += n * q.msz;
         }
         HIP_TRY(launch_iota(s->P[1], q.n, s->stream));
         // initial binning: positions in pid order, no jump; pids P1 -> P0,
@@ -900,16 +1052,35 @@ int check_inputs(const mtpt_params& p, const double* pos, const double* mass)
 {
     if (p.n > 0 && (!pos || !mass))
         return fail(MTPT_E_ARG, "pos and mass must not be NULL when n > 0");
-    for (int64_t i = 0; i < p.n; ++i)
-        for (int k = 0; k < p.dim; ++k) {
-            const double v = pos[i * p.dim + k];
-            if (!(v >= p.lo[k] && v <= p.hi[k]))
-                return fail(MTPT_E_ARG, "particle %lld coordinate %d = %g outside [%g, %g]",
-                            (long long)i, k, v, p.lo[k], p.hi[k]);
+    // the first coordinate outside the box and the first mass not finite
+    const int64_t none = std::numeric_limits<int64_t>::max();
+    std::atomic<int64_t> bad_pos{none}, bad_mass{none};
+    auto lower = [](std::atomic<int64_t>& a, int64_t v) {
+        int64_t o = a.load();
+        while (v < o && !a.compare_exchange_weak(o, v)) {
         }
-    for (int64_t i = 0; i < p.n * p.n_species; ++i)
-        if (!std::isfinite(mass[i]))
-            return fail(MTPT_E_ARG, "mass %lld is not finite", (long long)i);
+    };
+    parallel_ranges(p.n, kHostGrain, [&](int64_t b, int64_t e) {
+        for (int64_t i = b * p.dim, k = 0; i < e * p.dim; ++i, k = k + 1 < p.dim ? k + 1 : 0)
+            if (!(pos[i] >= p.lo[k] && pos[i] <= p.hi[k])) {
+                lower(bad_pos, i);
+                break;
+            }
+        for (int64_t c = 0; c < p.n_species; ++c)
+            for (int64_t i = c * p.n + b; i < c * p.n + e; ++i)
+                if (!std::isfinite(mass[i])) {
+                    lower(bad_mass, i);
+                    return;
+                }
+    });
+    if (bad_pos != none) {
+        const int64_t i = bad_pos / p.dim;
+        const int k = static_cast<int>(bad_pos % p.dim);
+        return fail(MTPT_E_ARG, "particle %lld coordinate %d = %g outside [%g, %g]", (long long)i, k,
+                    pos[bad_pos], p.lo[k], p.hi[k]);
+    }
+    if (bad_mass != none)
+        return fail(MTPT_E_ARG, "mass %lld is not finite", (long long)bad_mass.load());
     return MTPT_OK;
 }
 
@@ -1034,9 +1205,7 @@ int mtpt_masses(mtpt_sim* s, double* out)
     SimArgs a = base_args(s);
     hipError_t e = launch_unpermute_mass(s->q.prec, a, cur_mass(s), cur_pid(s), d, s->stream);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(out, d, bytes, hipMemcpyDeviceToHost, s->stream);
-    if (e == hipSuccess)
-        e = hipStreamSynchronize(s->stream);
+        e = copy_out(s, out, d, bytes);
     s->alloc.put(d);
     if (e != hipSuccess)
         return fail(MTPT_E_DEVICE, "mtpt_masses: %s", hipGetErrorString(e));
@@ -1061,9 +1230,7 @@ int mtpt_positions(mtpt_sim* s, double* out)
     SimArgs a = base_args(s);
     hipError_t e = launch_unpermute_pos(s->q.dim, s->q.prec, a, cur_pid(s), d, s->stream);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(out, d, bytes, hipMemcpyDeviceToHost, s->stream);
-    if (e == hipSuccess)
-        e = hipStreamSynchronize(s->stream);
+        e = copy_out(s, out, d, bytes);
     s->alloc.put(d);
     if (e != hipSuccess)
         return fail(MTPT_E_DEVICE, "mtpt_positions: %s", hipGetErrorString(e));

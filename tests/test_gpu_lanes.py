@@ -33,8 +33,9 @@ def test_lanes_equal_one_stream(mt, dims):
     reqs = [request(k, d) for k, d in enumerate(dims)]
     say(f"  lanes {dims}")
     got = []
+    alloc = mt.TorchAllocator("cuda:0")      # the library calls into it: it outlives the pools
     for stream in (None, torch.cuda.Stream()):
-        be = serve.PoolBackend(max_slots=2, allocator=mt.TorchAllocator("cuda:0"),
+        be = serve.PoolBackend(max_slots=2, allocator=alloc,
                                stream=stream.cuda_stream if stream is not None else None)
         rep = serve.serve(be, reqs)          # two slots: admitted as others finish
         be.close()
