@@ -16,8 +16,9 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 SOURCES = [os.path.join(CSRC, f) for f in (
     "mtpt_kernels.hip", "mtpt_runtime.hip",
-    "mtpt_tiles_2d_iso.hip", "mtpt_tiles_2d_tens.hip", "mtpt_tiles_3d_iso.hip", "mtpt_tiles_3d_tens.hip")]
-HEADERS = [os.path.join(CSRC, f) for f in ("mtpt_kernels.h", "mtpt_rng.h", "mtpt_device.h")] + \
+    "mtpt_tiles_2d_iso.hip", "mtpt_tiles_2d_tens.hip", "mtpt_tiles_3d_iso.hip", "mtpt_tiles_3d_tens.hip",
+    "mtpt_tiles_lists.hip")]
+HEADERS = [os.path.join(CSRC, f) for f in ("mtpt_kernels.h", "mtpt_rng.h", "mtpt_device.h", "mtpt_lists.h")] + \
     [os.path.join(ROOT, "include", "mtpt.h")]
 LIB = os.path.join(HERE, "libmtpt.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

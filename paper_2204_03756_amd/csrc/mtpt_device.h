@@ -923,17 +923,23 @@ __device__ __forceinline__ uint32_t bin_next(const SimArgs& a, uint32_t i, const
 // the pairs it would use -- a.nb_col == nullptr: their count plus one (self)
 // into a.nb_cnt[pid]; else the pids, self first, into a.nb_col from
 // a.nb_row[pid] -- and skips every store of the step.
-template <int D, int PREC, int NS, bool TRANSFER, bool TN, bool EXPORT = false>
+}  // namespace mtpt
+#include "mtpt_lists.h"
+namespace mtpt {
+
+template <int D, int PREC, int NS, bool TRANSFER, bool TN, bool EXPORT = false, bool LIST = false>
 __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
 {
     using T = typename Types<PREC>::T;
     using M = typename Types<PREC>::M;
-    constexpr int CAP = TileCap<D, PREC, NS, TRANSFER>::value;
+    static_assert(!LIST || (D == 3 && PREC == 0 && !TN), "neighbour lists: 3-d, FP64, isotropic");
+    constexpr int NT = LIST ? kListBlock : kBlock;
+    constexpr int CAP = LIST ? kListCap : TileCap<D, PREC, NS, TRANSFER>::value;
     constexpr int planes = D == 3 ? 3 : 1;
     constexpr int SCAP = TRANSFER ? CAP : 1;
     // rows are trimmed to the spherical cutoff's x-window; an ellipsoidal
     // cutoff scans its rows whole (the host never sets trim_rows for it)
-    constexpr bool kTrim = !TN;
+    constexpr bool kTrim = !TN && !LIST;
     // the FP64 row-sum pass evaluates its (software) exp only for the
     // candidates within the cutoff, after each chunk of 32, where rows are
     // not trimmed (about one candidate in six is in; in trimmed rows most
@@ -966,6 +972,8 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
     constexpr int kHist =
         TRANSFER ? (TileLimits<D>::max_x * TileLimits<D>::max_y * TileLimits<D>::max_z + 1) / 2 : 1;
     __shared__ uint32_t hist[kHist];
+    // list variant's row-sum pass: LDS offsets of every lane's neighbours
+    __shared__ uint16_t found[LIST && !TRANSFER ? kListDepth : 1][LIST && !TRANSFER ? NT : 1];
 
     const int tid = threadIdx.x;
     const int nc0 = a.nc[0], nc1 = a.nc[1], nc2 = a.nc[2];
@@ -998,7 +1006,7 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
     const int ncol = xb - xa;
     const int tw = x1 - x0;
     if (TRANSFER && a.fuse_bin)
-        for (int k = tid; k < (tw * nown + 1) / 2; k += kBlock)
+        for (int k = tid; k < (tw * nown + 1) / 2; k += NT)
             hist[k] = 0u;
 
     // Tile setup, bound by latency: two dependent rounds of global loads (the
@@ -1041,12 +1049,12 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
     // offsets are known.
     const int ncb = ncol + 1;
     constexpr int kCP = TileLimits<D>::col_p;
-    constexpr int kCstIt = (kSegs * kCP + kBlock - 1) / kBlock;
+    constexpr int kCstIt = (kSegs * kCP + NT - 1) / NT;
     const int cc = tid % kCP;
     uint32_t cv[kCstIt];
 #pragma unroll
     for (int it = 0; it < kCstIt; ++it) {
-        const int sg = (tid + it * kBlock) / kCP;
+        const int sg = (tid + it * NT) / kCP;
         const int pzr = D == 3 ? sg / kSY : 0;
         const int pyr = D == 3 ? sg % kSY : sg;
         const int pz = z0 - 1 + pzr;
@@ -1059,14 +1067,14 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
     if (cc == 0 || cc == ncol) {
 #pragma unroll
         for (int it = 0; it < kCstIt; ++it)
-            if ((tid + it * kBlock) / kCP < kSegs)
-                rbound[cc == 0 ? 0 : 1][(tid + it * kBlock) / kCP] = cv[it];
+            if ((tid + it * NT) / kCP < kSegs)
+                rbound[cc == 0 ? 0 : 1][(tid + it * NT) / kCP] = cv[it];
     }
     if (cc == x0 - xa || cc == x1 - xa) {
 #pragma unroll
         for (int it = 0; it < kCstIt; ++it)
-            if ((tid + it * kBlock) / kCP < kSegs)
-                rbound[cc == x0 - xa ? 2 : 3][(tid + it * kBlock) / kCP] = cv[it];
+            if ((tid + it * NT) / kCP < kSegs)
+                rbound[cc == x0 - xa ? 2 : 3][(tid + it * NT) / kCP] = cv[it];
     }
     __syncthreads();
     // lane r: halo row r, staged at LDS slots s_off .. from sorted slots s_off + s_dd ..;
@@ -1109,7 +1117,7 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
     // staging barrier)
 #pragma unroll
     for (int it = 0; it < kCstIt; ++it) {
-        const int sg = (tid + it * kBlock) / kCP;
+        const int sg = (tid + it * NT) / kCP;
         const uint32_t dd = from_lane(s_dd, static_cast<uint32_t>(sg & 63));
         if (sg < kSegs && cc < ncb)
             cst[sg][cc] = use_lds ? cv[it] - dd : cv[it];
@@ -1120,7 +1128,7 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
         if (tid < kRows)
             own_pre[tid] = o_pre;
         if (rows_tab)
-            for (int r = __builtin_amdgcn_readfirstlane(tid >> 6); r < kRows; r += kBlock / 64)
+            for (int r = __builtin_amdgcn_readfirstlane(tid >> 6); r < kRows; r += NT / 64)
                 for (uint32_t j = static_cast<uint32_t>(lane); j < lane_u32(o_len, r); j += 64)
                     row_of[lane_u32(o_pre, r) + j] = static_cast<uint8_t>(r);
     }
@@ -1129,21 +1137,21 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
         // stages slots tid, tid + kBlock, ...: it finds every slot's row
         // first (the searches advance together), then issues all its loads,
         // then all its LDS stores, so that its loads are in flight at once.
-        constexpr int kIt = (CAP + kBlock - 1) / kBlock;
+        constexpr int kIt = (CAP + NT - 1) / NT;
         T vx[kIt][D];
         T vs[kIt];
         M vm[kIt][NS];
         uint32_t slots[kIt], sdd[kIt];
 #pragma unroll
         for (int it = 0; it < kIt; ++it)
-            slots[it] = static_cast<uint32_t>(tid + it * kBlock);
+            slots[it] = static_cast<uint32_t>(tid + it * NT);
         find_rows(s_off, std::integral_constant<int, kSegs>{}, slots, sdd);
 #pragma unroll
         for (int it = 0; it < kIt; ++it)
             sdd[it] = from_lane(s_dd, sdd[it]);
 #pragma unroll
         for (int it = 0; it < kIt; ++it) {
-            const uint32_t slot = static_cast<uint32_t>(tid + it * kBlock);
+            const uint32_t slot = static_cast<uint32_t>(tid + it * NT);
             if (slot < total) {
                 const uint32_t g = slot + sdd[it];
 #pragma unroll
@@ -1159,7 +1167,7 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
         }
 #pragma unroll
         for (int it = 0; it < kIt; ++it) {
-            const uint32_t idx = static_cast<uint32_t>(tid + it * kBlock);
+            const uint32_t idx = static_cast<uint32_t>(tid + it * NT);
             if (idx < total) {
 #pragma unroll
                 for (int d = 0; d < D; ++d)
@@ -1182,7 +1190,7 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
                 obase[tid] = 0;
             __syncthreads();
             // own row r is halo row r + 1; own column cx is staged column x0 - xa + cx
-            for (int j = tid; j < tw * nrow; j += kBlock) {
+            for (int j = tid; j < tw * nrow; j += NT) {
                 const int r = j / tw;
                 const int cxr = x0 - xa + (j - r * tw);
                 const int cl = cxr > 0 ? cxr - 1 : 0;
@@ -1201,7 +1209,7 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
                 obase[tid] = wave_incl_scan(v) - v;
             }
             __syncthreads();
-            for (int j = tid; j < tw * nrow; j += kBlock) {
+            for (int j = tid; j < tw * nrow; j += NT) {
                 const int r = j / tw;
                 const int cxr = x0 - xa + (j - r * tw);
                 const uint32_t c0 = cst[r + 1][cxr];
@@ -1226,7 +1234,7 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
     // uniform, and the loop holds no workgroup barrier), so the wave-wide
     // maxima below see only live lanes.  A wave leaves once all its lanes are
     // past the last own particle.
-    for (uint32_t base = 0; base < own_total; base += kBlock) {
+    for (uint32_t base = 0; base < own_total; base += NT) {
         if (base + static_cast<uint32_t>(tid & ~63) >= own_total)
             break;
         const uint32_t t = base + tid;
@@ -1291,6 +1299,7 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
         constexpr bool kEarly = TRANSFER;
         T jv[3] = {T(0), T(0), T(0)};
         uint64_t mkp[planes], wkp[planes];
+        uint32_t lw[kListWords] = {};
 #pragma unroll
         for (int pzr = 0; pzr < planes; ++pzr)
             mkp[pzr] = wkp[pzr] = 0ull;
@@ -1309,12 +1318,18 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
                 for (int c = 0; c < NS; ++c)
                     acc.mi[c] = static_cast<const M*>(a.m_mid[c])[i];
             }
+            if constexpr (LIST) {
+                // (the last word only where a lane of the wave needs it)
+#pragma unroll
+                for (int w = 0; w < kListWords - 1; ++w)
+                    lw[w] = act ? list_word(a, w)[i] : 0u;
+            }
             if (kEarly && a.fuse_bin) {
 #pragma unroll
                 for (int d = 0; d < D; ++d)
                     jv[d] = static_cast<const T*>(a.jmp[d])[i];
             }
-            if (kEarly && act) {
+            if (!LIST && kEarly && act) {
 #pragma unroll
                 for (int pzr = 0; pzr < planes; ++pzr)
                     mkp[pzr] = a.cmask[static_cast<size_t>(pzr) * static_cast<size_t>(a.n) + i];
@@ -1325,7 +1340,25 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
                     wkp[pzr] = a.cwin[static_cast<size_t>(pzr) * static_cast<size_t>(a.n) + i];
             }
         }
-        if (use_lds) {
+        if constexpr (LIST) {
+            if (use_lds) {
+                auto export_slot = [&](uint32_t slot) {
+                    if constexpr (EXPORT) {
+                        int sgi = 0;
+                        for (int q = 1; q < kSegs; ++q)
+                            sgi = seg_off[q] <= slot ? q : sgi;
+                        record(seg_gb[sgi] + (slot - seg_off[sgi]));
+                    }
+                };
+                if constexpr (TRANSFER)
+                    list_transfer<NS, EXPORT, CAP>(a, lpos, lsr, lms, cst, rbase, cl, ch, lself, i, act, lw, xi, acc,
+                                                   export_slot);
+                else
+                    list_rowsum<EXPORT, CAP>(a, lpos, cst, found, rbase, cl, ch, lself, i, act, xi, acc,
+                                             export_slot);
+            }
+        }
+        if (!LIST && use_lds) {
             // LDS slot of particle i itself (the self pair is skipped by slot)
             const uint32_t li = lself;
             if constexpr (!TRANSFER)
@@ -1679,7 +1712,8 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
                 if (!TRANSFER && !EXPORT && act)
                     pmask[i] = tot <= 63u ? ((static_cast<uint64_t>(mhi) << 32) | mlo) : kMaskInvalid;
             }
-        } else {
+        }
+        if (!use_lds) {
 #pragma unroll
             for (int pzr = 0; pzr < planes; ++pzr) {
 #pragma unroll
@@ -1698,7 +1732,9 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
             }
             // no recorded neighbours or windows for the transfer pass (whose
             // tile may be staged)
-            if (!TRANSFER && !EXPORT && act) {
+            if (LIST && !TRANSFER && !EXPORT && act)
+                list_word(a, 0)[i] = kListNone;
+            if (!LIST && !TRANSFER && !EXPORT && act) {
 #pragma unroll
                 for (int pzr = 0; pzr < planes; ++pzr) {
                     a.cmask[static_cast<size_t>(pzr) * static_cast<size_t>(a.n) + i] = kMaskInvalid;
@@ -1773,7 +1809,7 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
         __syncthreads();
         const float inv_tw = 1.0f / static_cast<float>(tw);
         const float inv_nrow = 1.0f / static_cast<float>(nrow);
-        for (int k = tid; k < tw * nown; k += kBlock) {
+        for (int k = tid; k < tw * nown; k += NT) {
             const int rr = small_div(k, inv_tw);   // own row, y fastest (dense)
             const int rz = small_div(rr, inv_nrow);
             const uint32_t c = (static_cast<uint32_t>(z0 + rz) * nc1 + (y0 + rr - rz * nrow)) * nc0 + x0 + (k - rr * tw);
@@ -1781,11 +1817,11 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
         }
     }
     if constexpr (!TRANSFER) {
-        const uint32_t p = block_sum<kBlock, uint32_t>(pairs);
+        const uint32_t p = block_sum<NT, uint32_t>(pairs);
         if (tid == 0)
             a.pair_part[blk] = p;
     } else {
-        block_sum_n_final<kBlock, NS, double>(msum);
+        block_sum_n_final<NT, NS, double>(msum);
         if (tid == 0) {
 #pragma unroll
             for (int c = 0; c < NS; ++c)

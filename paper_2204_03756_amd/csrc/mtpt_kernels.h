@@ -112,6 +112,18 @@ template <int D, int PREC, int NS> struct LdsBudget {
 #define MTPT_ROW_GROUP_3D 4
 #endif
 
+// Neighbour-list variant of the 3-d FP64 passes (mtpt_lists.h): threads of a
+// workgroup (one pass over a tile of about 410 particles), particles a tile
+// stages (positions, row sums and three species: two workgroups per CU),
+// words and entries of a packed list, its count when a particle has none, and
+// rows of the row-sum pass's lists in LDS (a group of four past the end)
+constexpr int kListBlock = 512;
+constexpr int kListCap = 1330;
+constexpr int kListWords = 7;
+constexpr int kListMax = 2 + 3 * (kListWords - 1);
+constexpr uint32_t kListNone = 63u;
+constexpr int kListDepth = kListMax + 1 + 4;
+
 // Largest tile (cells in x, y and z) of the mass-transfer passes, the halo
 // cell rows it spans and the cell boundaries kept per halo row.  Halo rows
 // (segments) are numbered with a fixed pitch per plane, seg_y (a power of two
@@ -232,6 +244,7 @@ struct SimArgs {
     int32_t fuse_bin;        // the transfer pass also bins for the next step
     int32_t tcounts_valid;   // this step's binning came from the transfer pass:
                              // cell count = counts + tcounts
+    int32_t lists;           // the passes record and visit neighbour lists (mtpt_lists.h)
     int32_t trim_rows;       // trim candidate rows to the per-row x-window
     // dispersion tensor T = L L^T (shape of D_RW and D_MT): jumps L z, distance
     // q = |M dx|^2 with M = L^-1 (tensor == 0: isotropic, L = M = I unused)
@@ -288,6 +301,9 @@ hipError_t launch_phase_batched(int ph, int dim, int prec, int ns, int tn, const
 // tensor metric TN: one sim (a) or a batch (b, with a == nullptr)
 template <int D, bool TN>
 hipError_t launch_tiles(int ph, int prec, int ns, const SimArgs* a, const Batch* b, hipStream_t s);
+// the list variants of the two passes (a.lists), and their exports
+hipError_t launch_lists(int ph, int ns, const SimArgs& a, hipStream_t s);
+hipError_t launch_lists_export(int ph, int ns, const SimArgs& a, hipStream_t s);
 // the same passes recording the pairs they use (a.nb_* set), storing nothing
 template <int D, bool TN>
 hipError_t launch_tiles_export(int ph, int prec, int ns, const SimArgs& a, hipStream_t s);

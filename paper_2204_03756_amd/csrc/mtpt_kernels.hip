@@ -310,6 +310,8 @@ hipError_t launch_phase(int ph, int dim, int prec, const SimArgs& a, hipStream_t
     case PH_PLACE: MTPT_DISPATCH_D_PREC(place_k, grid, kBlock, a); break;
     case PH_ROWSUM:
     case PH_TRANSFER:
+        if (a.lists)
+            return launch_lists(ph, ns, a, s);
         if (dim == 2)
             return a.tensor ? launch_tiles<2, true>(ph, prec, ns, &a, nullptr, s)
                             : launch_tiles<2, false>(ph, prec, ns, &a, nullptr, s);

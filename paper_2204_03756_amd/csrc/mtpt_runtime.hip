@@ -123,6 +123,9 @@ struct Plan {
     uint32_t tiles_x = 1, tiles_y = 1, ntiles = 0;
     int ttile[3] = {1, 1, 1};                 // transfer pass
     uint32_t ttiles_x = 1, ttiles_y = 1, nttiles = 0;
+    bool lists = false;
+    int ltile[3] = {1, 1, 1};                 // both passes, with neighbour lists
+    uint32_t ltiles_x = 1, ltiles_y = 1, nltiles = 0;
     bool trim_rows = false;
     bool tensor = false;
     size_t tsz = 8, msz = 8;
@@ -277,7 +280,9 @@ int64_t tile_min_tiles()
     return 256;
 }
 
-Plan make_plan(const mtpt_params& p)
+// solo: the sim is stepped on its own (a pool's batches hold the mask variants
+// of the tiled passes only).
+Plan make_plan(const mtpt_params& p, bool solo)
 {
     Plan q;
     q.dim = p.dim;
@@ -410,6 +415,53 @@ Plan make_plan(const mtpt_params& p)
         // rows of three cells long enough that trimming them to the x-window
         // saves more candidates than its two binary searches cost
         q.trim_rows = !q.tensor && 3.0 * rho_c >= MTPT_TRIM_MIN_ROW;
+        // Neighbour lists (mtpt_lists.h) for the 3-d FP64 sims whose particles'
+        // neighbours fit a list, 4.5 standard deviations above their mean
+        // included, that fill half a workgroup per tile, and that have
+        // min_tiles such tiles: with fewer a launch lasts as long as its
+        // largest tile (reacting workload, us a step mask / list: 5e4
+        // particles, too few tiles, 58.6 / --, 7e4 65.6 / 51.5, 2e5 95 / 81,
+        // 1e6 258 / 206, 8e6 1895 / 1575; walks of 4e5 with 3, 4.4 and 5.4
+        // neighbours 108 / 101, 117 / 96, 121 / 110).  A pool's batches hold
+        // the mask variants only.
+        if (solo && q.dim == 3 && q.prec == MTPT_FP64 && !q.tensor && !q.trim_rows) {
+            double side3 = 1.0;
+            for (int k = 0; k < 3; ++k)
+                side3 *= (p.hi[k] - p.lo[k]) / q.nc[k];
+            const double mean = rho_c / side3 * 4.18879 * q.psi * q.psi * q.psi;
+            double best = 0.0;
+            int lt[3] = {1, 1, 1};
+            for (int z = 1; z <= std::min(q.nc[2], tile_max(3, 2)); ++z)
+                for (int y = 1; y <= std::min(q.nc[1], tile_max(3, 1)); ++y)
+                    for (int x = 1; x <= std::min(q.nc[0], tile_max(3, 0)); ++x) {
+                        const double halo = (x + 2.0) * (y + 2.0) * (z + 2.0) * rho_c;
+                        const double own = x * y * static_cast<double>(z) * rho_c;
+                        if (halo * 1.25 > kListCap || own + 2.0 * std::sqrt(own) > kListBlock)
+                            continue;
+                        const double cost = (64.0 * std::ceil(own / 64.0 + 0.5) + 0.1 * halo) / own;
+                        if (best == 0.0 || cost < best) {
+                            best = cost;
+                            lt[0] = x;
+                            lt[1] = y;
+                            lt[2] = z;
+                        }
+                    }
+            const double own = lt[0] * lt[1] * lt[2] * rho_c;
+            uint32_t lx = 0, ly = 0;
+            const uint32_t nlist = count(lt, &lx, &ly);
+            // the sim's memory is laid out for the mask variants' tiles: the
+            // pair counts go behind the partial sums of the fewer list tiles
+            const bool fits = static_cast<uint64_t>(nlist) * (q.ns * 8 + 4) <=
+                              static_cast<uint64_t>(std::max(q.part_blocks, q.nttiles)) * 24;
+            if (1.0 + mean + 4.5 * std::sqrt(mean) <= kListMax && own >= kListBlock / 2 && nlist >= min_tiles && fits) {
+                q.lists = true;
+                for (int k = 0; k < 3; ++k)
+                    q.ltile[k] = lt[k];
+                q.ltiles_x = lx;
+                q.ltiles_y = ly;
+                q.nltiles = nlist;
+            }
+        }
     }
     const size_t n = static_cast<size_t>(q.n);
     size_t off = 0;
@@ -445,6 +497,14 @@ Plan make_plan(const mtpt_params& p)
     q.off_pair = take(static_cast<size_t>(std::max<uint32_t>(q.ntiles, 1)) * 4);
     q.off_stats = take(sizeof(DevStats));
     q.bytes = off;
+    if (q.lists) {
+        for (int k = 0; k < 3; ++k)
+            q.tile[k] = q.ttile[k] = q.ltile[k];
+        q.tiles_x = q.ttiles_x = q.ltiles_x;
+        q.tiles_y = q.ttiles_y = q.ltiles_y;
+        q.ntiles = q.nttiles = q.nltiles;
+        q.off_pair = q.off_part + static_cast<size_t>(q.nltiles) * q.ns * 8;
+    }
     return q;
 }
 
@@ -564,6 +624,7 @@ SimArgs base_args(const mtpt_sim* s)
     a.ttiles_x = q.ttiles_x;
     a.ttiles_y = q.ttiles_y;
     a.nttiles = q.nttiles;
+    a.lists = q.lists ? 1 : 0;
     a.trim_rows = q.trim_rows ? 1 : 0;
     a.sdev = std::sqrt(2.0 * p.d_rw * p.dt);
     for (int k = 0; k < 3; ++k)
@@ -1105,7 +1166,7 @@ int new_sim(const mtpt_params* params, const double* pos, const double* mass, vo
         delete s;
         return fail(MTPT_E_DEVICE, "hipGetDevice failed");
     }
-    s->q = make_plan(s->p);
+    s->q = make_plan(s->p, st == nullptr);
     s->moving = s->p.d_rw > 0.0;
     for (int k = 0; k < params->dim; ++k)
         s->moving = s->moving || s->p.vel[k] != 0.0;
@@ -1156,7 +1217,7 @@ int mtpt_sim_bytes(const mtpt_params* params, size_t* bytes)
         return rc;
     if (!bytes)
         return fail(MTPT_E_ARG, "bytes is NULL");
-    *bytes = make_plan(*params).bytes;
+    *bytes = make_plan(*params, true).bytes;
     return MTPT_OK;
 }
 
@@ -1423,6 +1484,8 @@ int static_scratch(int device, char** out)
 hipError_t export_pass(const mtpt_sim* s, int ph, const SimArgs& a)
 {
     const int prec = s->q.prec, ns = s->q.ns;
+    if (s->q.lists)
+        return launch_lists_export(ph, ns, a, s->stream);
     if (s->q.dim == 2)
         return s->tens.on ? launch_tiles_export<2, true>(ph, prec, ns, a, s->stream)
                           : launch_tiles_export<2, false>(ph, prec, ns, a, s->stream);
@@ -1776,7 +1839,7 @@ int mtpt_pool_admit(mtpt_pool* p, const mtpt_params* params, const double* pos, 
     int rc = validate(params);
     if (rc)
         return rc;
-    const Plan q = make_plan(*params);
+    const Plan q = make_plan(*params, false);
     // the result export stages n*S doubles next to the sim
     const size_t need = q.bytes + static_cast<size_t>(q.n) * q.ns * 8;
     if (static_cast<int32_t>(p->sims.size()) >= p->max_slots)
