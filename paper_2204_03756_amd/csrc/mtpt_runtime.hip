@@ -1122,17 +1122,43 @@ int check_inputs(const mtpt_params& p, const double* pos, const double* mass)
         }
     };
     parallel_ranges(p.n, kHostGrain, [&](int64_t b, int64_t e) {
-        for (int64_t i = b * p.dim, k = 0; i < e * p.dim; ++i, k = k + 1 < p.dim ? k + 1 : 0)
-            if (!(pos[i] >= p.lo[k] && pos[i] <= p.hi[k])) {
-                lower(bad_pos, i);
-                break;
-            }
+        // a block's verdict without a branch per value; the place only of a bad one
+        constexpr int64_t kBlock = 512;
+        for (int64_t o = b; o < e; o += kBlock) {
+            const int64_t end = std::min(o + kBlock, e);
+            bool ok = true;
+            auto look = [&](auto dim) {
+                constexpr int D = decltype(dim)::value;
+                for (int64_t i = o; i < end; ++i)
+                    for (int k = 0; k < D; ++k)
+                        ok &= (pos[i * D + k] >= p.lo[k]) & (pos[i * D + k] <= p.hi[k]);
+            };
+            if (p.dim == 3)
+                look(std::integral_constant<int, 3>{});
+            else
+                look(std::integral_constant<int, 2>{});
+            if (ok)
+                continue;
+            int64_t i = o * p.dim;
+            while (pos[i] >= p.lo[i % p.dim] && pos[i] <= p.hi[i % p.dim])
+                ++i;
+            lower(bad_pos, i);
+            break;
+        }
         for (int64_t c = 0; c < p.n_species; ++c)
-            for (int64_t i = c * p.n + b; i < c * p.n + e; ++i)
-                if (!std::isfinite(mass[i])) {
-                    lower(bad_mass, i);
-                    return;
-                }
+            for (int64_t o = c * p.n + b; o < c * p.n + e; o += kBlock) {
+                const int64_t end = std::min(o + kBlock, c * p.n + e);
+                bool ok = true;
+                for (int64_t i = o; i < end; ++i)
+                    ok &= std::isfinite(mass[i]);
+                if (ok)
+                    continue;
+                int64_t i = o;
+                while (std::isfinite(mass[i]))
+                    ++i;
+                lower(bad_mass, i);
+                return;
+            }
     });
     if (bad_pos != none) {
         const int64_t i = bad_pos / p.dim;
