@@ -1882,6 +1882,38 @@ __device__ __forceinline__ int find_sim(const Batch& b, uint32_t blk, uint32_t* 
     return lo;
 }
 
+// The arguments of a tiled pass, read where they are used.  A tile's chain of
+// barriers, searches and candidate loops uses some sixty of them: taken by
+// value they are all loaded at the start and kept, in 106 scalar registers
+// and 40 to 140 spilled ones, each spill and its return an instruction of the
+// vector unit; taken from a batch's array, every load behind a store is a
+// vector load that waits for the memory.  Through the constant address space
+// (nothing writes them while the kernel runs) they are scalar loads wherever
+// they stand, and the hidden pointer keeps the compiler from gathering them at
+// the start again.  One word of each 64 bytes is read first, all at once: the
+// first use of a line would otherwise wait for the memory, in turn (1000
+// particles: row sum 7.1 us by value, 7.6 without, 7.2 with).  By value / so,
+// us a launch: 3-d transfer of 3.2e7 reacting particles 2065 / 1980, of a
+// 2e6-particle walk 184 / 177, 2-d FP64 transfer (1e4 particles) 11.2 / 8.4, 2-d
+// row sum (4e6) 75 / 72, 3-d (5e4) 37.9 / 34.9; batches of a pool, 2-d
+// transfer 45 / 31, 3-d 160 / 120.
+using ConstArgs = const __attribute__((address_space(4))) SimArgs;
+__device__ __forceinline__ const SimArgs& args_at(ConstArgs* p)
+{
+    using Word = const __attribute__((address_space(4))) uint32_t;
+    static_assert(sizeof(SimArgs) > 13 * 64 && sizeof(SimArgs) <= 14 * 64, "one word of each 64 bytes");
+    Word* w = (Word*)p;
+    asm volatile("" ::"s"(w[0]), "s"(w[16]), "s"(w[32]), "s"(w[48]), "s"(w[64]), "s"(w[80]), "s"(w[96]), "s"(w[112]),
+                 "s"(w[128]), "s"(w[144]), "s"(w[160]), "s"(w[176]), "s"(w[192]), "s"(w[208]));
+    asm volatile("" : "+s"(p));
+    return *(const SimArgs*)p;
+}
+// a single sim's kernel has them as its first argument
+__device__ __forceinline__ const SimArgs& kernel_args()
+{
+    return args_at((ConstArgs*)__builtin_amdgcn_kernarg_segment_ptr());
+}
+
 #define MTPT_BATCH_PROLOGUE                                                                     \
     uint32_t l;                                                                                 \
     const SimArgs& a = b.args[find_sim(b, xcd_block(blockIdx.x, gridDim.x), &l)]
@@ -1891,13 +1923,14 @@ __device__ __forceinline__ int find_sim(const Batch& b, uint32_t blk, uint32_t* 
 template <int D, int PREC, bool TN>
 __global__ __launch_bounds__(kBlock, D == 3 && PREC == 1 && !TN ? 7 : 1) void rowsum_k(SimArgs a)
 {
-    tile_body<D, PREC, 1, false, TN>(a, xcd_block(blockIdx.x, gridDim.x));
+    // (ellipsoidal cutoff: by value, 23.6 us against 24.1 at 5e5 particles in 2-d)
+    tile_body<D, PREC, 1, false, TN>(TN ? a : kernel_args(), xcd_block(blockIdx.x, gridDim.x));
 }
 template <int D, int PREC, bool TN>
 __global__ __launch_bounds__(kBlock, D == 3 && PREC == 1 && !TN ? 7 : 1) void rowsum_kb(Batch b)
 {
     MTPT_BATCH_PROLOGUE;
-    tile_body<D, PREC, 1, false, TN>(a, l);
+    tile_body<D, PREC, 1, false, TN>(args_at((ConstArgs*)&a), l);
 }
 
 // the 2-d FP64 one-species transfer kernel is held to the registers of 5
@@ -1926,13 +1959,13 @@ __global__ __launch_bounds__(kBlock, (transfer_min_blocks<D, PREC, NS>())) void 
         --blk;
         --n;
     }
-    tile_body<D, PREC, NS, true, TN>(a, xcd_block(blk, n));
+    tile_body<D, PREC, NS, true, TN>(kernel_args(), xcd_block(blk, n));
 }
 template <int D, int PREC, int NS, bool TN>
 __global__ __launch_bounds__(kBlock, (transfer_min_blocks<D, PREC, NS>())) void transfer_kb(Batch b)
 {
     MTPT_BATCH_PROLOGUE;
-    tile_body<D, PREC, NS, true, TN>(a, l);
+    tile_body<D, PREC, NS, true, TN>(args_at((ConstArgs*)&a), l);
 }
 
 // Launch of the row-sum (ph = PH_ROWSUM) or transfer (PH_TRANSFER) pass of

@@ -8,7 +8,7 @@ namespace mtpt {
 // the four waves per SIMD that their LDS allows.
 __global__ __launch_bounds__(kListBlock, 4) void rowsum_list_k(SimArgs a)
 {
-    tile_body<3, 0, 1, false, false, false, true>(a, xcd_block(blockIdx.x, gridDim.x));
+    tile_body<3, 0, 1, false, false, false, true>(kernel_args(), xcd_block(blockIdx.x, gridDim.x));
 }
 template <int NS>
 __global__ __launch_bounds__(kListBlock, 4) void transfer_list_k(SimArgs a)
@@ -22,7 +22,7 @@ __global__ __launch_bounds__(kListBlock, 4) void transfer_list_k(SimArgs a)
         --blk;
         --n;
     }
-    tile_body<3, 0, NS, true, false, false, true>(a, xcd_block(blk, n));
+    tile_body<3, 0, NS, true, false, false, true>(kernel_args(), xcd_block(blk, n));
 }
 __global__ __launch_bounds__(kListBlock) void rowsum_list_export_k(SimArgs a)
 {
