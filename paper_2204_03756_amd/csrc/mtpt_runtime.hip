@@ -55,14 +55,22 @@ int fail(int code, const char* fmt, ...)
 // Host threads of a large conversion or copy (memory-bound: a few saturate it).
 constexpr int kHostThreads = 8;
 
-// f(begin, end) over [0, n) in one range per thread, at least grain items
-// each, on this thread alone when that is one range.  A thread that cannot be
-// started runs its range here.  f must not throw.
+// Inputs of at least this many bytes are read by several threads.  Smaller ones
+// are often still in the caller's cache, and a caller that makes its next
+// inputs in the same memory would have to fetch those lines back from the other
+// cores: measured with 10 to 30 MB inputs, the caller's own generation of the
+// next ones took 12.4 ms instead of 7.8, and 105 instead of 77 for 16 sims,
+// more than the 8 ms that the threads saved.
+constexpr size_t kHostThreaded = static_cast<size_t>(64) << 20;
+
+// f(begin, end) over [0, n), items of bytes in all, in one range per thread, on
+// this thread alone below kHostThreaded.  A thread that cannot be started runs
+// its range here.  f must not throw.
 template <typename F>
-void parallel_ranges(int64_t n, int64_t grain, F f)
+void parallel_ranges(int64_t n, size_t bytes, F f)
 {
     const int64_t cpus = static_cast<int64_t>(std::max(1u, std::thread::hardware_concurrency()));
-    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>({kHostThreads, cpus, n / grain}));
+    const int64_t parts = bytes < kHostThreaded ? 1 : std::max<int64_t>(1, std::min<int64_t>({kHostThreads, cpus, n}));
     std::thread th[kHostThreads];
     for (int64_t t = 1; t < parts; ++t) {
         const int64_t b = n * t / parts, e = n * (t + 1) / parts;
@@ -77,9 +85,8 @@ void parallel_ranges(int64_t n, int64_t grain, F f)
         if (x.joinable())
             x.join();
 }
-// particles per thread below which a thread costs more than it saves (about
-// 30 us to start one, 2.4 ns to check and convert a particle)
-constexpr int64_t kHostGrain = 65536;
+// bytes of a sim's inputs
+inline size_t input_bytes(const mtpt_params& p) { return static_cast<size_t>(p.n) * (p.dim + p.n_species) * 8; }
 
 struct Alloc {
     mtpt_allocator a{};
@@ -1045,9 +1052,11 @@ int create_into(mtpt_sim* s, const double* pos, const double* mass, PinnedStage*
             // the pinned staging holds every array at once: [dim][n]
             // positions, then [ns][n] masses
             unsigned char* const hm = stage + q.dim * n * q.tsz;
-            parallel_ranges(q.n, kHostGrain, [&](int64_t b, int64_t e) {
-                for (int k = 0; k < q.dim; ++k)
-                    put_pos(stage + k * n * q.tsz, k, b, e);
+            parallel_ranges(q.n, input_bytes(s->p), [&](int64_t b, int64_t e) {
+                // (every coordinate of a block while it is in the cache)
+                for (int64_t o = b; o < e; o += 1024)
+                    for (int k = 0; k < q.dim; ++k)
+                        put_pos(stage + k * n * q.tsz, k, o, std::min<int64_t>(o + 1024, e));
                 for (int c = 0; c < q.ns; ++c)
                     put_mass(hm + c * n * q.msz, c, b, e);
             });
@@ -1058,13 +1067,13 @@ int create_into(mtpt_sim* s, const double* pos, const double* mass, PinnedStage*
         } else {
             // the pageable one holds one array at a time (its copy blocks)
             for (int k = 0; k < q.dim; ++k) {
-                parallel_ranges(q.n, kHostGrain, [&](int64_t b, int64_t e) { put_pos(stage, k, b, e); });
+                parallel_ranges(q.n, input_bytes(s->p), [&](int64_t b, int64_t e) { put_pos(stage, k, b, e); });
                 HIP_TRY(hipMemcpy(s->X[k], stage, n * q.tsz, hipMemcpyHostToDevice));
             }
             for (int c = 0; c < q.ns; ++c) {
                 const void* src = mass + c * n;
                 if (q.msz == 4) {
-                    parallel_ranges(q.n, kHostGrain, [&](int64_t b, int64_t e) { put_mass(stage, c, b, e); });
+                    parallel_ranges(q.n, input_bytes(s->p), [&](int64_t b, int64_t e) { put_mass(stage, c, b, e); });
                     src = stage;
                 }
                 HIP_TRY(hipMemcpy(s->M[1][c], src, n * q.msz, hipMemcpyHostToDevice));
@@ -1121,7 +1130,7 @@ int check_inputs(const mtpt_params& p, const double* pos, const double* mass)
         while (v < o && !a.compare_exchange_weak(o, v)) {
         }
     };
-    parallel_ranges(p.n, kHostGrain, [&](int64_t b, int64_t e) {
+    parallel_ranges(p.n, input_bytes(p), [&](int64_t b, int64_t e) {
         // a block's verdict without a branch per value; the place only of a bad one
         constexpr int64_t kBlock = 512;
         for (int64_t o = b; o < e; o += kBlock) {

@@ -35,6 +35,27 @@ def test_first_fault_is_reported(bad, message):
     assert lib.mtpt_last_error().decode() == message
 
 
+@pytest.mark.parametrize("i,k,c,j", [(0, 0, 2, 1_499_999), (187_500, 2, 1, 187_499), (1_499_999, 1, 0, 749_999)])
+def test_first_fault_of_several_threads(i, k, c, j):
+    """67 MiB of inputs: eight ranges, faults at their edges and in more than one."""
+    lib = mtpt.load()
+    n = 1_500_000
+    x, m = np.full((n, 3), 0.25), np.ones((3, n))
+    p = mtpt.make_params(_params(n, 3, 3))
+
+    def create():
+        h = C.c_void_p()
+        rc = lib.mtpt_create(C.byref(p), x.ctypes.data_as(mtpt._f64p), m.ctypes.data_as(mtpt._f64p), None, None,
+                             C.byref(h))
+        assert rc == mtpt.MTPT_E_ARG and not h.value
+        return lib.mtpt_last_error().decode()
+
+    m[c, j] = m[2, n - 1] = np.inf
+    assert create() == f"mass {c * n + j} is not finite"
+    x[i, k] = x[n - 1, 2] = -0.5
+    assert create() == f"particle {i} coordinate {k} = -0.5 outside [0, 1]"
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,dim,ns,prec", [(2_800_001, 3, 3, W.FP64), (4_200_003, 2, 1, W.FP64),
                                            (2_900_003, 3, 1, W.FP32_KAHAN), (70_001, 2, 3, W.FP32W_FP64ACC)])
