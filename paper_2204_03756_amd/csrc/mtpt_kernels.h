@@ -62,10 +62,12 @@ constexpr uint32_t kScanFold = 2048;  // scans of at most this many tiles skip t
 #define MTPT_LDS_BUDGET_3D_WIDE 46080
 #endif
 // 3-d three-species FP32-position transfer pass: with 32 KiB and its candidate
-// loop unrolled by 2 (114 VGPRs) it holds four workgroups per CU (measured
-// 2.13 ms per launch on the 3.2e7-particle reacting workload, against 2.24 ms
-// with 45 KiB tiles at three workgroups per CU; 32 KiB unrolled by 4 at
-// three workgroups: 2.54 ms)
+// loop unrolled by 2 (108 VGPRs) it holds four workgroups per CU.  Measured on
+// the 3.2e7-particle reacting workload: 1.98 ms a launch; with 34.8 KB tiles,
+// also four workgroups, 2.09 ms; with 26.6 KB tiles and the registers held to
+// five, 2.81 ms; unrolled by 3 or 4, 1.98 and 1.97 ms (before its arguments left
+// the registers, 114 VGPRs: 2.13 ms, 2.24 ms with 45 KiB tiles at three
+// workgroups, 2.54 ms unrolled by 4, at three)
 #ifndef MTPT_LDS_BUDGET_3D_S3
 #define MTPT_LDS_BUDGET_3D_S3 32768
 #endif

@@ -343,6 +343,11 @@ Plan make_plan(const mtpt_params& p, bool solo)
     // tile that way is cut into at least min_tiles tiles (or one tile per
     // cell): its step time is then the time of one small tile, not that of a
     // few large tiles on a mostly idle chip.
+    size_t room_part = 0, room_pair = 0;
+    // bytes of the workgroups' sums: of the set-up totals and of a step
+    auto part_bytes = [&]() {
+        return align_up(static_cast<size_t>(std::max(q.part_blocks, q.nttiles)) * q.ns * 8, 256);
+    };
     {
         const double rho_c = static_cast<double>(q.n) / static_cast<double>(q.ncells);
         const int64_t min_tiles = tile_min_tiles();
@@ -366,8 +371,9 @@ Plan make_plan(const mtpt_params& p, bool solo)
 #ifndef MTPT_TILE_LANES
 #define MTPT_TILE_LANES 64.0
 #endif
-        // the tile shape for a staging capacity of capn particles
-        auto choose = [&](int capn, int* t) {
+        // the tile shape for a staging capacity of capn particles, own particles
+        // in waves or (few, see MTPT_LAT_TILES) in whole workgroups of lanes
+        auto choose = [&](int capn, bool few, int* t) {
             const double cap = static_cast<double>(capn) / 1.25;
             int tx = 1, ty = 1, tz = 1;
             if (q.dim == 2) {
@@ -392,7 +398,8 @@ Plan make_plan(const mtpt_params& p, bool solo)
                             if ((halo > cap || tiles_of(x, y, z) < min_tiles) && !unit)
                                 continue;
                             const double own = std::max(1e-9, x * y * static_cast<double>(z) * rho_c);
-                            const double lanes = tiles_of(x, y, z) < MTPT_LAT_TILES ? static_cast<double>(kBlock) : MTPT_TILE_LANES;
+                            const double lanes =
+                                few && tiles_of(x, y, z) < MTPT_LAT_TILES ? static_cast<double>(kBlock) : MTPT_TILE_LANES;
                             const double passes = std::ceil((own + 2.0 * std::sqrt(own)) / lanes);
                             const double cost = (passes * lanes + 0.02 * halo + 25.0) / own;
                             if (best == 0.0 || cost < best) {
@@ -407,18 +414,32 @@ Plan make_plan(const mtpt_params& p, bool solo)
             t[1] = ty;
             t[2] = tz;
         };
-        // the row-sum pass stages positions only (its capacity is that of the
-        // one-species transfer pass); the transfer pass stages row sums and
-        // every species too
-        choose(tile_capacity(q.dim, q.prec, 1), q.tile);
-        choose(tile_capacity(q.dim, q.prec, q.ns), q.ttile);
         auto count = [&](const int* t, uint32_t* txs, uint32_t* tys) {
             *txs = static_cast<uint32_t>((q.nc[0] + t[0] - 1) / t[0]);
             *tys = static_cast<uint32_t>((q.nc[1] + t[1] - 1) / t[1]);
             return *txs * *tys * static_cast<uint32_t>(q.dim == 3 ? (q.nc[2] + t[2] - 1) / t[2] : 1);
         };
-        q.ntiles = count(q.tile, &q.tiles_x, &q.tiles_y);
-        q.nttiles = count(q.ttile, &q.ttiles_x, &q.ttiles_y);
+        // the row-sum pass stages positions only (its capacity is that of the
+        // one-species transfer pass); the transfer pass stages row sums and
+        // every species too
+        auto shapes = [&](bool few) {
+            choose(tile_capacity(q.dim, q.prec, 1), few, q.tile);
+            choose(tile_capacity(q.dim, q.prec, q.ns), few, q.ttile);
+            q.ntiles = count(q.tile, &q.tiles_x, &q.tiles_y);
+            q.nttiles = count(q.ttile, &q.ttiles_x, &q.ttiles_y);
+        };
+        // The per-tile sums and counts have the room that the shapes in waves
+        // need (three sums a tile, whatever the species), so that a sim's bytes
+        // do not depend on the rule for few tiles; three-species sims whose
+        // shapes by that rule would need more keep the others.
+        shapes(false);
+        room_part = align_up(static_cast<size_t>(std::max<uint32_t>(std::max(q.part_blocks, q.nttiles), 1)) * 24, 256);
+        room_pair = align_up(static_cast<size_t>(std::max<uint32_t>(q.ntiles, 1)) * 4, 256);
+        if (q.dim == 3) {
+            shapes(true);
+            if (part_bytes() > room_part || part_bytes() + q.ntiles * 4u > room_part + room_pair)
+                shapes(false);
+        }
         // rows of three cells long enough that trimming them to the x-window
         // saves more candidates than its two binary searches cost
         q.trim_rows = !q.tensor && 3.0 * rho_c >= MTPT_TRIM_MIN_ROW;
@@ -458,8 +479,7 @@ Plan make_plan(const mtpt_params& p, bool solo)
             const uint32_t nlist = count(lt, &lx, &ly);
             // the sim's memory is laid out for the mask variants' tiles: the
             // pair counts go behind the partial sums of the fewer list tiles
-            const bool fits = static_cast<uint64_t>(nlist) * (q.ns * 8 + 4) <=
-                              static_cast<uint64_t>(std::max(q.part_blocks, q.nttiles)) * 24;
+            const bool fits = static_cast<uint64_t>(nlist) * (q.ns * 8 + 4) <= room_part;
             if (1.0 + mean + 4.5 * std::sqrt(mean) <= kListMax && own >= kListBlock / 2 && nlist >= min_tiles && fits) {
                 q.lists = true;
                 for (int k = 0; k < 3; ++k)
@@ -500,8 +520,10 @@ Plan make_plan(const mtpt_params& p, bool solo)
     q.off_tcounts = take(padded * 4);
     q.off_starts = take(padded * 4);
     q.off_bsum = take(static_cast<size_t>(q.scan_blocks) * 4);
-    q.off_part = take(static_cast<size_t>(std::max<uint32_t>(std::max(q.part_blocks, q.nttiles), 1)) * 3 * 8);
-    q.off_pair = take(static_cast<size_t>(std::max<uint32_t>(q.ntiles, 1)) * 4);
+    q.off_part = take(room_part);
+    q.off_pair = take(room_pair);
+    if (part_bytes() > room_part || q.ntiles * 4u > room_pair)
+        q.off_pair = q.off_part + part_bytes();
     q.off_stats = take(sizeof(DevStats));
     q.bytes = off;
     if (q.lists) {
