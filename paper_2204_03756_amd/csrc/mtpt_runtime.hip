@@ -69,8 +69,11 @@ constexpr size_t kHostThreaded = static_cast<size_t>(64) << 20;
 template <typename F>
 void parallel_ranges(int64_t n, size_t bytes, F f)
 {
+    if (bytes < kHostThreaded || n < kHostThreads)
+        return f(0, n);
+    // (asked for here only: the answer is read from a file, some 15 us)
     const int64_t cpus = static_cast<int64_t>(std::max(1u, std::thread::hardware_concurrency()));
-    const int64_t parts = bytes < kHostThreaded ? 1 : std::max<int64_t>(1, std::min<int64_t>({kHostThreads, cpus, n}));
+    const int64_t parts = std::min<int64_t>(kHostThreads, cpus);
     std::thread th[kHostThreads];
     for (int64_t t = 1; t < parts; ++t) {
         const int64_t b = n * t / parts, e = n * (t + 1) / parts;
@@ -80,7 +83,7 @@ void parallel_ranges(int64_t n, size_t bytes, F f)
             f(b, e);
         }
     }
-    f(0, parts > 1 ? n / parts : n);
+    f(0, n / parts);
     for (auto& x : th)
         if (x.joinable())
             x.join();
