@@ -287,6 +287,24 @@ int mtpt_pool_usage(mtpt_pool* pool, int32_t* active, size_t* bytes_held, size_t
  * parameter checks of mtpt_create. */
 int mtpt_sim_bytes(const mtpt_params* params, size_t* bytes);
 
+/* How a sim's mass-transfer passes are cut up (measurement and tests, no
+ * passage of the paper): cells of a workgroup's tile along each axis and the
+ * number of tiles, of the row-sum and the transfer pass, and whether the two
+ * hand over packed neighbour lists (3-d, MTPT_FP64).  Results do not depend
+ * on it, but for the grouping of the FP64 totals. */
+typedef struct {
+    int32_t tile[3], ttile[3];
+    int64_t tiles, ttiles;
+    int32_t lists;
+} mtpt_plan_t;
+
+/* The plan of a sim with these params alone, before its particles are seen.
+ * Errors as the parameter checks of mtpt_create. */
+int mtpt_plan(const mtpt_params* params, mtpt_plan_t* out);
+
+/* The plan that a sim runs by. */
+int mtpt_sim_plan(const mtpt_sim* sim, mtpt_plan_t* out);
+
 /* Free every sim of the pool and the pool (synchronises first).  NULL is a
  * no-op. */
 int mtpt_pool_destroy(mtpt_pool* pool);

@@ -540,6 +540,17 @@ Plan make_plan(const mtpt_params& p, bool solo)
     return q;
 }
 
+void describe(const Plan& q, mtpt_plan_t* out)
+{
+    for (int k = 0; k < 3; ++k) {
+        out->tile[k] = q.tile[k];
+        out->ttile[k] = q.ttile[k];
+    }
+    out->tiles = q.ntiles;
+    out->ttiles = q.nttiles;
+    out->lists = q.lists ? 1 : 0;
+}
+
 struct PhaseEv {
     int phase;
     hipEvent_t a, b;
@@ -1278,6 +1289,25 @@ int mtpt_sim_bytes(const mtpt_params* params, size_t* bytes)
     if (!bytes)
         return fail(MTPT_E_ARG, "bytes is NULL");
     *bytes = make_plan(*params, true).bytes;
+    return MTPT_OK;
+}
+
+int mtpt_plan(const mtpt_params* params, mtpt_plan_t* out)
+{
+    const int rc = validate(params);
+    if (rc)
+        return rc;
+    if (!out)
+        return fail(MTPT_E_ARG, "out is NULL");
+    describe(make_plan(*params, true), out);
+    return MTPT_OK;
+}
+
+int mtpt_sim_plan(const mtpt_sim* s, mtpt_plan_t* out)
+{
+    if (!s || !out)
+        return fail(MTPT_E_ARG, "NULL argument");
+    describe(s->q, out);
     return MTPT_OK;
 }
 

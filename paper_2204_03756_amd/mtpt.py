@@ -57,6 +57,11 @@ class mtpt_stats_t(C.Structure):
     ]
 
 
+class mtpt_plan_t(C.Structure):
+    _fields_ = [("tile", C.c_int32 * 3), ("ttile", C.c_int32 * 3), ("tiles", C.c_int64), ("ttiles", C.c_int64),
+                ("lists", C.c_int32)]
+
+
 _LIB = None
 _f64p = C.POINTER(C.c_double)
 _i64p = C.POINTER(C.c_int64)
@@ -103,6 +108,8 @@ def load():
         "mtpt_pool_stats": (C.c_int, [C.c_void_p, C.c_int64, P(mtpt_stats_t)]),
         "mtpt_pool_usage": (C.c_int, [C.c_void_p, P(C.c_int32), P(C.c_size_t), P(C.c_size_t)]),
         "mtpt_sim_bytes": (C.c_int, [P(mtpt_params), P(C.c_size_t)]),
+        "mtpt_plan": (C.c_int, [P(mtpt_params), P(mtpt_plan_t)]),
+        "mtpt_sim_plan": (C.c_int, [C.c_void_p, P(mtpt_plan_t)]),
         "mtpt_pool_destroy": (C.c_int, [C.c_void_p]),
     }
     for name, (res, args) in sig.items():
@@ -286,6 +293,22 @@ def mtpt_sim_bytes(params) -> int:
     b = C.c_size_t()
     _check(load().mtpt_sim_bytes(C.byref(q), C.byref(b)))
     return int(b.value)
+
+
+def _plan_dict(q) -> dict:
+    return {"tile": list(q.tile), "ttile": list(q.ttile), "tiles": q.tiles, "ttiles": q.ttiles, "lists": bool(q.lists)}
+
+
+def mtpt_plan(params) -> dict:
+    q, out = params if isinstance(params, mtpt_params) else make_params(params), mtpt_plan_t()
+    _check(load().mtpt_plan(C.byref(q), C.byref(out)))
+    return _plan_dict(out)
+
+
+def mtpt_sim_plan(sim) -> dict:
+    out = mtpt_plan_t()
+    _check(load().mtpt_sim_plan(sim, C.byref(out)))
+    return _plan_dict(out)
 
 
 def mtpt_pool_create(hbm_budget: int, max_slots: int, hip_stream=None,

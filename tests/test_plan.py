@@ -1,0 +1,28 @@
+"""The tile plans of the mass-transfer passes, as mtpt_plan states them (host
+arithmetic: no GPU)."""
+import ctypes as C
+
+import pytest
+
+from paper_2204_03756_amd import mtpt, workloads as W
+
+
+def _cube(n, per_unit, ns, prec, d_mt, dt, **kw):
+    """A 3-d sim of n particles, per_unit of them in a unit of volume."""
+    side = (n / per_unit) ** (1.0 / 3.0)
+    return W.Params(dim=3, n=n, lo=[0.0] * 3, hi=[side] * 3, d_rw=d_mt, d_mt=d_mt, dt=dt, n_species=ns, precision=prec,
+                    **kw)
+
+
+def test_plan_covers_the_grid_and_checks_its_arguments():
+    p = _cube(100_003, 1.0, 3, W.FP64, 0.7, 0.05)
+    plan = mtpt.mtpt_plan(p)
+    nc = [int(p.hi[k] / (p.psi_eff * (1 + 1e-6))) for k in range(3)]
+    for tile, tiles in ((plan["tile"], plan["tiles"]), (plan["ttile"], plan["ttiles"])):
+        assert tiles == -(-nc[0] // tile[0]) * -(-nc[1] // tile[1]) * -(-nc[2] // tile[2])
+    lib, q = mtpt.load(), mtpt.make_params(p)
+    assert lib.mtpt_plan(C.byref(q), None) == mtpt.MTPT_E_ARG
+    assert lib.mtpt_sim_plan(None, C.byref(mtpt.mtpt_plan_t())) == mtpt.MTPT_E_ARG
+    q.dt = 0.0
+    with pytest.raises(mtpt.MtptError):
+        mtpt.mtpt_plan(q)
