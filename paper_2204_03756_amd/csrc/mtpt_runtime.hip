@@ -361,13 +361,16 @@ Plan make_plan(const mtpt_params& p, bool solo)
 #ifndef MTPT_TILE_OWN
 #define MTPT_TILE_OWN 640.0
 #endif
-// Tiles below which (eight per compute unit) a 3-d tile's own particles are
-// counted in whole workgroups of lanes instead of waves: with so few tiles the
-// launch lasts as long as its slowest workgroup, and a second pass over the
-// particles that holds a few waves doubles that (measured, us a step with
-// waves / with workgroups: 1e5-particle walk Kahan 92 / 77, reacting 1e5 FP64
-// 75 / 69, 6e4 FP32W 52 / 48.6, 4e5 93 / 87; 3e5 Kahan 120.6 / 122).  At 4096
-// the reacting 1e6 FP64 step lost 4 %, at 1024 the 3e5 ones 7-10 %.
+// A 3-d pass that waves would cut into fewer tiles than this (eight per compute
+// unit) counts a tile's own particles in whole workgroups of lanes instead: with
+// so few tiles the launch lasts as long as its slowest workgroup, and a second
+// pass over the particles that holds a few waves doubles that (us a step with
+// waves / with workgroups: walk Kahan 1e5 92 / 75, 4.9e5 172 / 164, FP64 2e5
+// 178 / 171, 2.4e5 211 / 189, reacting FP32W 5e4 49 / 45, Kahan 3.4e5 90 / 84).
+// At 4096 the reacting 1e6 FP64 step lost 4 %, at 1024 the walk of 3e5 7-10 %.
+// The pass's own count decides, not each shape's: with the latter a shape just
+// above the line was priced in waves against others in workgroups, and FP64
+// walks of 2e5 to 2.4e5 got tiles of 105 particles (219 and 240 us a step).
 #ifndef MTPT_LAT_TILES
 #define MTPT_LAT_TILES 2048
 #endif
@@ -401,8 +404,7 @@ Plan make_plan(const mtpt_params& p, bool solo)
                             if ((halo > cap || tiles_of(x, y, z) < min_tiles) && !unit)
                                 continue;
                             const double own = std::max(1e-9, x * y * static_cast<double>(z) * rho_c);
-                            const double lanes =
-                                few && tiles_of(x, y, z) < MTPT_LAT_TILES ? static_cast<double>(kBlock) : MTPT_TILE_LANES;
+                            const double lanes = few ? static_cast<double>(kBlock) : MTPT_TILE_LANES;
                             const double passes = std::ceil((own + 2.0 * std::sqrt(own)) / lanes);
                             const double cost = (passes * lanes + 0.02 * halo + 25.0) / own;
                             if (best == 0.0 || cost < best) {
@@ -425,9 +427,9 @@ Plan make_plan(const mtpt_params& p, bool solo)
         // the row-sum pass stages positions only (its capacity is that of the
         // one-species transfer pass); the transfer pass stages row sums and
         // every species too
-        auto shapes = [&](bool few) {
+        auto shapes = [&](bool few, bool tfew) {
             choose(tile_capacity(q.dim, q.prec, 1), few, q.tile);
-            choose(tile_capacity(q.dim, q.prec, q.ns), few, q.ttile);
+            choose(tile_capacity(q.dim, q.prec, q.ns), tfew, q.ttile);
             q.ntiles = count(q.tile, &q.tiles_x, &q.tiles_y);
             q.nttiles = count(q.ttile, &q.ttiles_x, &q.ttiles_y);
         };
@@ -435,13 +437,14 @@ Plan make_plan(const mtpt_params& p, bool solo)
         // need (three sums a tile, whatever the species), so that a sim's bytes
         // do not depend on the rule for few tiles; three-species sims whose
         // shapes by that rule would need more keep the others.
-        shapes(false);
+        shapes(false, false);
         room_part = align_up(static_cast<size_t>(std::max<uint32_t>(std::max(q.part_blocks, q.nttiles), 1)) * 24, 256);
         room_pair = align_up(static_cast<size_t>(std::max<uint32_t>(q.ntiles, 1)) * 4, 256);
-        if (q.dim == 3) {
-            shapes(true);
+        const bool few = q.dim == 3 && q.ntiles < MTPT_LAT_TILES, tfew = q.dim == 3 && q.nttiles < MTPT_LAT_TILES;
+        if (few || tfew) {
+            shapes(few, tfew);
             if (part_bytes() > room_part || part_bytes() + q.ntiles * 4u > room_part + room_pair)
-                shapes(false);
+                shapes(false, false);
         }
         // rows of three cells long enough that trimming them to the x-window
         // saves more candidates than its two binary searches cost

@@ -26,3 +26,15 @@ def test_plan_covers_the_grid_and_checks_its_arguments():
     q.dt = 0.0
     with pytest.raises(mtpt.MtptError):
         mtpt.mtpt_plan(q)
+
+
+@pytest.mark.parametrize("n", [120_001, 175_693, 203_301, 224_999, 241_927, 282_953, 342_375])
+def test_tiles_on_both_sides_of_the_rule_for_few_tiles(n):
+    """FP64 walks of one particle in a unit of volume: tiles for every compute
+    unit to spare, so none of less than half a workgroup.  (The rule for few
+    tiles once priced shapes past its line in waves and the others in
+    workgroups, and took tiles of 105 particles.)"""
+    plan = mtpt.mtpt_plan(_cube(n, 1.0, 1, W.FP64, 1.0, 0.1))
+    nc = int((n ** (1.0 / 3.0)) / (3.0 * 0.4 ** 0.5 * (1 + 1e-6)))
+    for t in (plan["tile"], plan["ttile"]):
+        assert t[0] * t[1] * t[2] * n / nc ** 3 >= 128, plan
