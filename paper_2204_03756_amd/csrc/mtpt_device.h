@@ -953,7 +953,8 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
     constexpr int kRows = TileLimits<D>::own_rows;   // own rows (pitch kSY per plane)
     constexpr int kSY = TileLimits<D>::seg_y;
     static_assert(kSegs <= 64, "a lane of a wave stands for each halo row");
-    __shared__ uint32_t rbound[4][kSegs];
+    constexpr bool kHalves = LIST && TRANSFER && !EXPORT;   // sums of two transfer tiles (mtpt_lists.h)
+    __shared__ uint32_t rbound[kHalves ? 5 : 4][kSegs];
     __shared__ uint32_t cst[kSegs][TileLimits<D>::cols];
     __shared__ uint32_t seg_gb[EXPORT ? kSegs : 1], seg_off[EXPORT ? kSegs : 1];
     // 2-d FP64 row-sum pass: own cells in order of their candidate count, so
@@ -978,9 +979,10 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
     const int tid = threadIdx.x;
     const int nc0 = a.nc[0], nc1 = a.nc[1], nc2 = a.nc[2];
     // this pass's tile plan
-    const int* const tl = TRANSFER ? a.ttile : a.tile;
-    const uint32_t tiles_x = TRANSFER ? a.ttiles_x : a.tiles_x;
-    const uint32_t per_slab = tiles_x * (TRANSFER ? a.ttiles_y : a.tiles_y);
+    constexpr bool kOwnPlan = TRANSFER && !LIST;
+    const int* const tl = kOwnPlan ? a.ttile : a.tile;
+    const uint32_t tiles_x = kOwnPlan ? a.ttiles_x : a.tiles_x;
+    const uint32_t per_slab = tiles_x * (kOwnPlan ? a.ttiles_y : a.tiles_y);
     const int tzi = static_cast<int>(blk / per_slab);
     const uint32_t rem = blk - static_cast<uint32_t>(tzi) * per_slab;
     const int tyi = static_cast<int>(rem / tiles_x);
@@ -1076,6 +1078,14 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
             if ((tid + it * NT) / kCP < kSegs)
                 rbound[cc == x0 - xa ? 2 : 3][(tid + it * NT) / kCP] = cv[it];
     }
+    if constexpr (kHalves) {
+        if (cc == min(x0 + a.ttile[0], x1) - xa) {
+#pragma unroll
+            for (int it = 0; it < kCstIt; ++it)
+                if ((tid + it * NT) / kCP < kSegs)
+                    rbound[4][(tid + it * NT) / kCP] = cv[it];
+        }
+    }
     __syncthreads();
     // lane r: halo row r, staged at LDS slots s_off .. from sorted slots s_off + s_dd ..;
     // own row r, own particles o_pre .., their sorted slots o_pre + o_dd ..,
@@ -1098,6 +1108,13 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
             o_gb = rbound[2][o_seg];
             o_len = rbound[3][o_seg] - o_gb;
         }
+    }
+    // list variant: the part of own row r in the first of the two transfer tiles
+    uint32_t a_len = 0;
+    if constexpr (kHalves) {
+        const int rr = lane < kRows ? lane : 0;
+        const bool first = (a.lsplit != 1 || rr % kSY < a.ttile[1]) && (a.lsplit != 2 || rr / kSY < a.ttile[2]);
+        a_len = a.lsplit == 0 ? min(o_len, rbound[4][o_seg] - o_gb) : (first ? o_len : 0u);
     }
     const uint32_t o_inc = wave_incl_scan(o_len);
     const uint32_t o_pre = o_inc - o_len;
@@ -1820,6 +1837,52 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
         const uint32_t p = block_sum<NT, uint32_t>(pairs);
         if (tid == 0)
             a.pair_part[blk] = p;
+    } else if constexpr (LIST) {
+        const uint32_t a_inc = wave_incl_scan(a_len);
+        const uint32_t a_pre = a_inc - a_len, a_total = lane_u32(a_inc, 63);
+        // the transfer tile that this thread sums for
+        const bool upper = __builtin_amdgcn_readfirstlane(tid / kBlock) != 0;
+        const uint32_t v = static_cast<uint32_t>(tid % kBlock);
+        const uint32_t count = upper ? own_total - a_total : a_total;
+        auto row_at = [&](uint32_t start, uint32_t k) {
+            const uint32_t at[1] = {k};
+            uint32_t row[1];
+            find_rows(start, std::integral_constant<int, kRows>{}, at, row);
+            return row[0];
+        };
+        double sum[NS] = {};
+        __syncthreads();                     // (the staged masses are read no more)
+        if (own_total <= static_cast<uint32_t>(NT)) {
+            // each thread's mass to its place in its transfer tile's order
+            const uint32_t t = min(static_cast<uint32_t>(tid), own_total > 0u ? own_total - 1u : 0u);
+            const uint32_t r = row_at(o_pre, t);
+            const uint32_t op = from_lane(o_pre, r), ap = from_lane(a_pre, r), al = from_lane(a_len, r);
+            const uint32_t to = t - op < al ? ap + (t - op) : a_total + (op - ap) + (t - op - al);
+            if (static_cast<uint32_t>(tid) < own_total)
+#pragma unroll
+                for (int c = 0; c < NS; ++c)
+                    lms[c][to] = msum[c];
+            __syncthreads();
+            for (uint32_t k = v; k < count; k += kBlock)
+#pragma unroll
+                for (int c = 0; c < NS; ++c)
+                    sum[c] += lms[c][(upper ? a_total : 0u) + k];
+        } else {
+            for (uint32_t k0 = 0; k0 < count; k0 += kBlock) {
+                const uint32_t k = min(k0 + v, count - 1u);
+                const uint32_t r = row_at(upper ? o_pre - a_pre : a_pre, k);
+                const uint32_t op = from_lane(o_pre, r), ap = from_lane(a_pre, r), al = from_lane(a_len, r);
+                const uint32_t i = from_lane(o_dd, r) + op + (upper ? al + (k - (op - ap)) : k - ap);
+                if (k0 + v < count)
+#pragma unroll
+                    for (int c = 0; c < NS; ++c)
+                        sum[c] += static_cast<const double*>(a.m_dst[c])[i];
+            }
+        }
+        const int sub[3] = {txi * (a.lsplit == 0 ? 2 : 1) + (upper && a.lsplit == 0 ? 1 : 0),
+                            tyi * (a.lsplit == 1 ? 2 : 1) + (upper && a.lsplit == 1 ? 1 : 0),
+                            tzi * (a.lsplit == 2 ? 2 : 1) + (upper && a.lsplit == 2 ? 1 : 0)};
+        list_totals<NS>(a, upper, sub, sum);
     } else {
         block_sum_n_final<NT, NS, double>(msum);
         if (tid == 0) {

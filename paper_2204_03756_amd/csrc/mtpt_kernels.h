@@ -124,6 +124,7 @@ constexpr int kListCap = 1330;
 constexpr int kListWords = 7;
 constexpr int kListMax = 2 + 3 * (kListWords - 1);
 constexpr uint32_t kListNone = 63u;
+constexpr int kListWhole = 3;       // SimArgs::lsplit of tiles that are one transfer tile
 constexpr int kListDepth = kListMax + 1 + 4;
 
 // Largest tile (cells in x, y and z) of the mass-transfer passes, the halo
@@ -247,6 +248,7 @@ struct SimArgs {
     int32_t tcounts_valid;   // this step's binning came from the transfer pass:
                              // cell count = counts + tcounts
     int32_t lists;           // the passes record and visit neighbour lists (mtpt_lists.h)
+    int32_t lsplit;          // axis along which a list tile is two transfer tiles, kListWhole: one
     int32_t trim_rows;       // trim candidate rows to the per-row x-window
     // dispersion tensor T = L L^T (shape of D_RW and D_MT): jumps L z, distance
     // q = |M dx|^2 with M = L^-1 (tensor == 0: isotropic, L = M = I unused)

@@ -39,6 +39,46 @@ __device__ __forceinline__ uint32_t* list_word(const SimArgs& a, int w)
                               : a.perm;
 }
 
+// A list tile is one tile of the mask variant's transfer pass, or two of them
+// side by side (a.lsplit: the axis, kListWhole: one), and leaves their partial
+// sums: the totals of a sim are then the same bit for bit whichever variant it
+// takes, alone or in a pool.  The mask variant sums a tile by thread (particles
+// v, v + kBlock, .. in the tile's order), by wave and over its kBlock / 64
+// waves; here each half of the workgroup sums one transfer tile in that order,
+// the masses handed over through LDS, or, of a tile of more particles than the
+// workgroup has threads, read back.
+// The sums of a transfer tile's kBlock threads (sum) to its place in a.partials.
+template <int NS>
+__device__ __forceinline__ void list_totals(const SimArgs& a, bool upper, const int* sub, const double* sum)
+{
+    constexpr int kWaves = kBlock / 64;
+    __shared__ double red[NS][kListBlock / 64];
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int c = 0; c < NS; ++c) {
+        double x = sum[c];
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1)
+            x += __shfl_down(x, off, 64);
+        if ((tid & 63) == 0)
+            red[c][tid >> 6] = x;
+    }
+    __syncthreads();
+    // (the second tile may lie past the grid's edge)
+    if (tid % kBlock != 0 || (upper && a.lsplit == kListWhole) || sub[0] * a.ttile[0] >= a.nc[0] ||
+        sub[1] * a.ttile[1] >= a.nc[1] || sub[2] * a.ttile[2] >= a.nc[2])
+        return;
+    const size_t s = (static_cast<size_t>(sub[2]) * a.ttiles_y + sub[1]) * a.ttiles_x + sub[0];
+#pragma unroll
+    for (int c = 0; c < NS; ++c) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w)
+            t += red[c][(upper ? kWaves : 0) + w];
+        a.partials[s * NS + c] = t;
+    }
+}
+
 // words that a list of cnt entries takes
 __device__ __forceinline__ uint32_t list_words(uint32_t cnt) { return cnt <= 2u ? 1u : 1u + cnt / 3u; }
 

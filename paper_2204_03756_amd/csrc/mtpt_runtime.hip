@@ -133,9 +133,8 @@ struct Plan {
     uint32_t tiles_x = 1, tiles_y = 1, ntiles = 0;
     int ttile[3] = {1, 1, 1};                 // transfer pass
     uint32_t ttiles_x = 1, ttiles_y = 1, nttiles = 0;
-    bool lists = false;
-    int ltile[3] = {1, 1, 1};                 // both passes, with neighbour lists
-    uint32_t ltiles_x = 1, ltiles_y = 1, nltiles = 0;
+    bool lists = false;                       // neighbour lists: tile is both passes' tile, of one
+    int lsplit = kListWhole;                  // transfer tile or two along this axis
     bool trim_rows = false;
     bool tensor = false;
     size_t tsz = 8, msz = 8;
@@ -347,10 +346,12 @@ Plan make_plan(const mtpt_params& p, bool solo)
     // cell): its step time is then the time of one small tile, not that of a
     // few large tiles on a mostly idle chip.
     size_t room_part = 0, room_pair = 0;
-    // bytes of the workgroups' sums: of the set-up totals and of a step
+    // bytes of the workgroups' sums: of the set-up totals and of a step, of a
+    // step alone
     auto part_bytes = [&]() {
         return align_up(static_cast<size_t>(std::max(q.part_blocks, q.nttiles)) * q.ns * 8, 256);
     };
+    auto step_bytes = [&]() { return static_cast<size_t>(q.nttiles) * q.ns * 8; };
     {
         const double rho_c = static_cast<double>(q.n) / static_cast<double>(q.ncells);
         const int64_t min_tiles = tile_min_tiles();
@@ -451,48 +452,69 @@ Plan make_plan(const mtpt_params& p, bool solo)
         q.trim_rows = !q.tensor && 3.0 * rho_c >= MTPT_TRIM_MIN_ROW;
         // Neighbour lists (mtpt_lists.h) for the 3-d FP64 sims whose particles'
         // neighbours fit a list, 4.5 standard deviations above their mean
-        // included, that fill half a workgroup per tile, and that have
-        // min_tiles such tiles: with fewer a launch lasts as long as its
-        // largest tile (reacting workload, us a step mask / list: 5e4
-        // particles, too few tiles, 58.6 / --, 7e4 65.6 / 51.5, 2e5 95 / 81,
-        // 1e6 258 / 206, 8e6 1895 / 1575; walks of 4e5 with 3, 4.4 and 5.4
-        // neighbours 108 / 101, 117 / 96, 121 / 110).  A pool's batches hold
-        // the mask variants only.
-        if (solo && q.dim == 3 && q.prec == MTPT_FP64 && !q.tensor && !q.trim_rows) {
+        // included, with tiles that fill half a workgroup, of which there are
+        // min_tiles: with fewer a launch lasts as long as its largest tile
+        // (reacting workload, us a step mask / list: 2e5 particles 100 / 88, 1e6
+        // 274 / 229, 4e6 969 / 867).  A list tile is one transfer tile or two
+        // along an axis.  Of the shapes that suit the mask variant as well as
+        // the one chosen above (as few tiles, as much room for a denser place:
+        // with 12 % larger halos and 25 % more particles than the mean in a
+        // place its 1e6-particle step took 395 us instead of 314), the pair with
+        // the least estimated list cost is taken, by the mask variant too, so
+        // that both leave the same partial sums.  Tiles of 11 x 6 x 5 cells, not
+        // two of anything, were 4 % faster at 8e6 particles, 1 % at 1e6.
+        if (q.dim == 3 && q.prec == MTPT_FP64 && !q.tensor && !q.trim_rows) {
             double side3 = 1.0;
             for (int k = 0; k < 3; ++k)
                 side3 *= (p.hi[k] - p.lo[k]) / q.nc[k];
             const double mean = rho_c / side3 * 4.18879 * q.psi * q.psi * q.psi;
+            auto own_of = [&](const int* t) { return t[0] * t[1] * static_cast<double>(t[2]) * rho_c; };
+            auto halo_of = [&](const int* t) { return (t[0] + 2.0) * (t[1] + 2.0) * (t[2] + 2.0) * rho_c; };
+            const double halo_max = halo_of(q.ttile);
             double best = 0.0;
-            int lt[3] = {1, 1, 1};
+            int tt[3] = {1, 1, 1}, lt[3] = {1, 1, 1};
+            uint32_t lx = 0, ly = 0;
             for (int z = 1; z <= std::min(q.nc[2], tile_max(3, 2)); ++z)
                 for (int y = 1; y <= std::min(q.nc[1], tile_max(3, 1)); ++y)
                     for (int x = 1; x <= std::min(q.nc[0], tile_max(3, 0)); ++x) {
-                        const double halo = (x + 2.0) * (y + 2.0) * (z + 2.0) * rho_c;
-                        const double own = x * y * static_cast<double>(z) * rho_c;
-                        if (halo * 1.25 > kListCap || own + 2.0 * std::sqrt(own) > kListBlock)
+                        const int t[3] = {x, y, z};
+                        const double sub = own_of(t);
+                        if (halo_of(t) > halo_max || count(t, &lx, &ly) > q.nttiles)
                             continue;
-                        const double cost = (64.0 * std::ceil(own / 64.0 + 0.5) + 0.1 * halo) / own;
-                        if (best == 0.0 || cost < best) {
-                            best = cost;
-                            lt[0] = x;
-                            lt[1] = y;
-                            lt[2] = z;
+                        for (int axis = 0; axis <= kListWhole; ++axis) {
+                            int l[3] = {x, y, z};
+                            if (axis < kListWhole)
+                                l[axis] *= 2;
+                            const double own = own_of(l), halo = halo_of(l);
+                            if (axis < kListWhole && (l[axis] > tile_max(3, axis) || sub + 2.0 * std::sqrt(sub) > kBlock))
+                                continue;
+                            if (halo * 1.25 > kListCap || own + 2.0 * std::sqrt(own) > kListBlock || own < kListBlock / 2)
+                                continue;
+                            const uint32_t nl = count(l, &lx, &ly);
+                            const double cost = nl * (64.0 * std::ceil(own / 64.0 + 0.5) + 0.1 * halo);
+                            if (nl < min_tiles)
+                                continue;
+                            if (best == 0.0 || cost < best) {
+                                best = cost;
+                                q.lsplit = axis;
+                                std::copy(t, t + 3, tt);
+                                std::copy(l, l + 3, lt);
+                            }
                         }
                     }
-            const double own = lt[0] * lt[1] * lt[2] * rho_c;
-            uint32_t lx = 0, ly = 0;
             const uint32_t nlist = count(lt, &lx, &ly);
-            // the sim's memory is laid out for the mask variants' tiles: the
-            // pair counts go behind the partial sums of the fewer list tiles
-            const bool fits = static_cast<uint64_t>(nlist) * (q.ns * 8 + 4) <= room_part;
-            if (1.0 + mean + 4.5 * std::sqrt(mean) <= kListMax && own >= kListBlock / 2 && nlist >= min_tiles && fits) {
-                q.lists = true;
-                for (int k = 0; k < 3; ++k)
-                    q.ltile[k] = lt[k];
-                q.ltiles_x = lx;
-                q.ltiles_y = ly;
-                q.nltiles = nlist;
+            // (the sim's memory is laid out for the mask variants' tiles)
+            const bool fits = step_bytes() + nlist * 4u <= room_part + room_pair;
+            if (best > 0.0 && 1.0 + mean + 4.5 * std::sqrt(mean) <= kListMax && fits) {
+                std::copy(tt, tt + 3, q.ttile);
+                q.nttiles = count(q.ttile, &q.ttiles_x, &q.ttiles_y);
+                if (solo) {
+                    q.lists = true;
+                    std::copy(lt, lt + 3, q.tile);
+                    q.tiles_x = lx;
+                    q.tiles_y = ly;
+                    q.ntiles = nlist;
+                }
             }
         }
     }
@@ -528,18 +550,11 @@ Plan make_plan(const mtpt_params& p, bool solo)
     q.off_bsum = take(static_cast<size_t>(q.scan_blocks) * 4);
     q.off_part = take(room_part);
     q.off_pair = take(room_pair);
-    if (part_bytes() > room_part || q.ntiles * 4u > room_pair)
-        q.off_pair = q.off_part + part_bytes();
+    const size_t sums = q.lists ? step_bytes() : part_bytes();
+    if (sums > room_part || q.ntiles * 4u > room_pair)
+        q.off_pair = q.off_part + sums;
     q.off_stats = take(sizeof(DevStats));
     q.bytes = off;
-    if (q.lists) {
-        for (int k = 0; k < 3; ++k)
-            q.tile[k] = q.ttile[k] = q.ltile[k];
-        q.tiles_x = q.ttiles_x = q.ltiles_x;
-        q.tiles_y = q.ttiles_y = q.ltiles_y;
-        q.ntiles = q.nttiles = q.nltiles;
-        q.off_pair = q.off_part + static_cast<size_t>(q.nltiles) * q.ns * 8;
-    }
     return q;
 }
 
@@ -671,6 +686,7 @@ SimArgs base_args(const mtpt_sim* s)
     a.ttiles_y = q.ttiles_y;
     a.nttiles = q.nttiles;
     a.lists = q.lists ? 1 : 0;
+    a.lsplit = q.lsplit;
     a.trim_rows = q.trim_rows ? 1 : 0;
     a.sdev = std::sqrt(2.0 * p.d_rw * p.dt);
     for (int k = 0; k < 3; ++k)

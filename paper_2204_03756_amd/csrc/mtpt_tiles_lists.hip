@@ -36,7 +36,7 @@ __global__ __launch_bounds__(kListBlock) void transfer_list_export_k(SimArgs a)
 
 hipError_t launch_lists(int ph, int ns, const SimArgs& a, hipStream_t s)
 {
-    const uint32_t grid = ph == PH_ROWSUM ? a.ntiles : a.nttiles + (a.fin_partials ? 1u : 0u);
+    const uint32_t grid = a.ntiles + (ph == PH_TRANSFER && a.fin_partials ? 1u : 0u);
     if (grid == 0 || a.n <= 0)
         return hipSuccess;
     if (ph == PH_ROWSUM) rowsum_list_k<<<grid, kListBlock, 0, s>>>(a);
@@ -48,7 +48,7 @@ hipError_t launch_lists(int ph, int ns, const SimArgs& a, hipStream_t s)
 
 hipError_t launch_lists_export(int ph, int ns, const SimArgs& a, hipStream_t s)
 {
-    const uint32_t grid = ph == PH_ROWSUM ? a.ntiles : a.nttiles;
+    const uint32_t grid = a.ntiles;
     if (grid == 0 || a.n <= 0)
         return hipSuccess;
     if (ph == PH_ROWSUM) rowsum_list_export_k<<<grid, kListBlock, 0, s>>>(a);
