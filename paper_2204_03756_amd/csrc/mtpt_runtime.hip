@@ -486,7 +486,8 @@ Plan make_plan(const mtpt_params& p, bool solo)
                             if (axis < kListWhole)
                                 l[axis] *= 2;
                             const double own = own_of(l), halo = halo_of(l);
-                            if (axis < kListWhole && (l[axis] > tile_max(3, axis) || sub + 2.0 * std::sqrt(sub) > kBlock))
+                            if (axis < kListWhole && (l[axis] > tile_max(3, axis) || t[axis] >= q.nc[axis] ||
+                                                      sub + 2.0 * std::sqrt(sub) > kBlock))
                                 continue;
                             if (halo * 1.25 > kListCap || own + 2.0 * std::sqrt(own) > kListBlock || own < kListBlock / 2)
                                 continue;

@@ -18,8 +18,8 @@ def mt():
 
 
 # (particles, box, species, axis of the two transfer tiles (None: one), particles in the first tile's cells)
-CASES = [(971, [6.1, 11.6, 15.8], 1, 0, 0), (9001, [20.8, 20.8, 20.8], 3, 0, 0), (1411, [8.8, 12.6, 22.8], 3, 0, 420),
-         (1189, [14.7, 10.7, 8.0], 1, 1, 0), (1267, [19.0, 5.2, 15.0], 3, 1, 0), (1331, [16.3, 23.0, 3.4], 1, 2, 0),
+CASES = [(899, [18.1, 5.3, 13.1], 1, 0, 0), (9001, [20.8, 20.8, 20.8], 3, 0, 0), (1411, [8.8, 12.6, 22.8], 3, 0, 420),
+         (1189, [14.7, 10.7, 8.0], 1, 1, 0), (1267, [19.0, 5.2, 15.0], 3, 1, 0), (1155, [8.4, 16.9, 10.2], 1, 2, 0),
          (1189, [8.8, 7.2, 23.5], 3, 2, 0), (1051, [20.4, 7.1, 10.6], 1, None, 0), (1101, [13.3, 15.8, 11.6], 3, None, 560)]
 
 
