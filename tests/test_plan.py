@@ -40,16 +40,13 @@ def test_tiles_on_both_sides_of_the_rule_for_few_tiles(n):
         assert t[0] * t[1] * t[2] * n / nc ** 3 >= 128, plan
 
 
-@pytest.mark.parametrize("thick", [1.2, 2.3, 3.5, 4.6])
-def test_list_tiles_are_doubled_inside_the_grid_only(thick, monkeypatch):
-    """Slabs of one to four cells: two transfer tiles make a list tile along an
-    axis where the grid has two."""
+@pytest.mark.parametrize("n,hi,ns", [(971, [6.1, 11.6, 15.8], 1), (1331, [16.3, 23.0, 3.4], 1), (1081, [17.8, 3.0, 18.9], 3)])
+def test_list_tiles_are_doubled_inside_the_grid_only(n, hi, ns, monkeypatch):
+    """Boxes as thin as their transfer tile: two of them make a list tile along
+    an axis where the grid has two."""
     monkeypatch.setenv("MTPT_MIN_TILES", "1")
-    for k in range(1, 9):
-        side = 8.0 * k
-        p = W.Params(dim=3, n=int(side * side * thick), lo=[0.0] * 3, hi=[side, side, thick], d_rw=0.3, d_mt=1.1 ** 2 / 3.6,
-                     dt=0.1, psi=1.1, n_species=3, precision=W.FP64)
-        plan = mtpt.mtpt_plan(p)
-        for axis in range(3):
-            if plan["tile"][axis] != plan["ttile"][axis] and plan["lists"]:
-                assert plan["ttile"][axis] < int(p.hi[axis] / (1.1 * (1 + 1e-6))), plan
+    plan = mtpt.mtpt_plan(W.Params(dim=3, n=n, lo=[0.0] * 3, hi=hi, d_rw=0.3, d_mt=1.1 ** 2 / 3.6, dt=0.1, psi=1.1,
+                                   n_species=ns, precision=W.FP64))
+    for axis in range(3):
+        if plan["lists"] and plan["tile"][axis] != plan["ttile"][axis]:
+            assert plan["ttile"][axis] < int(hi[axis] / (1.1 * (1 + 1e-6))), plan
