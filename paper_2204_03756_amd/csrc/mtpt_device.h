@@ -1749,8 +1749,12 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
             }
             // no recorded neighbours or windows for the transfer pass (whose
             // tile may be staged)
-            if (LIST && !TRANSFER && !EXPORT && act)
-                list_word(a, 0)[i] = kListNone;
+            if constexpr (LIST && !TRANSFER && !EXPORT) {
+                if (act) {
+                    list_word(a, 0)[i] = kListNone;
+                    count_unlisted(a, acc.cnt);
+                }
+            }
             if (!LIST && !TRANSFER && !EXPORT && act) {
 #pragma unroll
                 for (int pzr = 0; pzr < planes; ++pzr) {

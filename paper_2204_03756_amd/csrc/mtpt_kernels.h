@@ -156,6 +156,8 @@ struct DevStats {
     unsigned long long pairs_last;   // pairs of the last step
     unsigned long long pairs_total;  // over all steps
     int nonfinite;                   // sticky: a total was NaN or infinite
+    unsigned int unlisted;           // particles that a row-sum pass found no list for (mtpt_lists.h)
+    unsigned int most_pairs;         // most neighbours of one of them, itself included
     int pad0;
     double totals[3];                // mass totals after the last step
     long long steps;                 // steps completed on the device

@@ -28,7 +28,8 @@
 // candidate row; words 0..5 are the masks' memory, word 6 is the permutation
 // of the binning, free between the place pass and the next scatter.  A
 // particle with more neighbours, or slots further apart, has the count
-// kListNone, and the transfer pass scans its rows.
+// kListNone, and the transfer pass scans its rows.  That is slower than the
+// masks, so the host keeps the lists to sims with few such particles.
 #pragma once
 
 namespace mtpt {
@@ -77,6 +78,13 @@ __device__ __forceinline__ void list_totals(const SimArgs& a, bool upper, const 
             t += red[c][(upper ? kWaves : 0) + w];
         a.partials[s * NS + c] = t;
     }
+}
+
+// a particle without a list, of cnt neighbours, itself included
+__device__ __forceinline__ void count_unlisted(const SimArgs& a, uint32_t cnt)
+{
+    atomicAdd(&a.st->unlisted, 1u);
+    atomicMax(&a.st->most_pairs, cnt);
 }
 
 // words that a list of cnt entries takes
@@ -200,8 +208,9 @@ __device__ __forceinline__ void list_rowsum(const SimArgs& a, const double (*lpo
         if (!EXPORT && act)
             list_word(a, static_cast<int>(w))[i] = v;
     }
+    const bool none = over || far > 1023u;
     if (!EXPORT && act)
-        list_word(a, 0)[i] = over || far > 1023u ? kListNone : w0;
+        list_word(a, 0)[i] = none ? kListNone : w0;
     acc.s = s;
     acc.cnt = cnt;
     if (over) {
@@ -215,6 +224,8 @@ __device__ __forceinline__ void list_rowsum(const SimArgs& a, const double (*lpo
                 export_slot(slot);
         }
     }
+    if (!EXPORT && act && none)
+        count_unlisted(a, acc.cnt);
 }
 
 // Mass increments of one particle per lane from its list (lw: its words but

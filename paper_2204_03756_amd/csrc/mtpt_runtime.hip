@@ -289,9 +289,9 @@ int64_t tile_min_tiles()
     return 256;
 }
 
-// solo: the sim is stepped on its own (a pool's batches hold the mask variants
-// of the tiled passes only).
-Plan make_plan(const mtpt_params& p, bool solo)
+// lists: neighbour lists if the sim suits them (a pool's batches and sims of
+// crowded particles take the mask variants of the tiled passes).
+Plan make_plan(const mtpt_params& p, bool lists)
 {
     Plan q;
     q.dim = p.dim;
@@ -462,7 +462,9 @@ Plan make_plan(const mtpt_params& p, bool solo)
         // place its 1e6-particle step took 395 us instead of 314), the pair with
         // the least estimated list cost is taken, by the mask variant too, so
         // that both leave the same partial sums.  Tiles of 11 x 6 x 5 cells, not
-        // two of anything, were 4 % faster at 8e6 particles, 1 % at 1e6.
+        // two of anything, were 4 % faster at 8e6 particles, 1 % at 1e6.  Sims that
+        // a drift gathers at the walls keep the masks, as do those whose
+        // particles are found crowded at create (kListShare).
         if (q.dim == 3 && q.prec == MTPT_FP64 && !q.tensor && !q.trim_rows) {
             double side3 = 1.0;
             for (int k = 0; k < 3; ++k)
@@ -471,6 +473,7 @@ Plan make_plan(const mtpt_params& p, bool solo)
             auto own_of = [&](const int* t) { return t[0] * t[1] * static_cast<double>(t[2]) * rho_c; };
             auto halo_of = [&](const int* t) { return (t[0] + 2.0) * (t[1] + 2.0) * (t[2] + 2.0) * rho_c; };
             const double halo_max = halo_of(q.ttile);
+            const bool drift = p.vel[0] != 0.0 || p.vel[1] != 0.0 || p.vel[2] != 0.0;
             double best = 0.0;
             int tt[3] = {1, 1, 1}, lt[3] = {1, 1, 1};
             uint32_t lx = 0, ly = 0;
@@ -509,7 +512,7 @@ Plan make_plan(const mtpt_params& p, bool solo)
             if (best > 0.0 && 1.0 + mean + 4.5 * std::sqrt(mean) <= kListMax && fits) {
                 std::copy(tt, tt + 3, q.ttile);
                 q.nttiles = count(q.ttile, &q.ttiles_x, &q.ttiles_y);
-                if (solo) {
+                if (lists && !drift) {
                     q.lists = true;
                     std::copy(lt, lt + 3, q.tile);
                     q.tiles_x = lx;
@@ -569,6 +572,16 @@ void describe(const Plan& q, mtpt_plan_t* out)
     out->ttiles = q.nttiles;
     out->lists = q.lists ? 1 : 0;
 }
+
+// A sim of which more than one particle in kListShare has no list at create, or
+// one of them has more than kListCrowd neighbours, takes the masks: a wave that
+// holds one scans its rows without a list, and a small sim's launch waits for it
+// (us a step lists / masks: 2e5 reacting particles, even 88 / 99, 0.1 % in clumps
+// of 20 89 / 97, of 40 96 / 98, a single clump of 70 118 / 103, of 100 141 / 105, a
+// fifth in clumps of 25 145 / 119; 1e6, even 227 / 274, 0.1 % in clumps of 40 240 /
+// 267, five of 100 282 / 268, a Gaussian plume 1645 / 1469).
+constexpr uint64_t kListShare = 1000;
+constexpr uint32_t kListCrowd = 48;
 
 struct PhaseEv {
     int phase;
@@ -1152,6 +1165,9 @@ int create_into(mtpt_sim* s, const double* pos, const double* mass, PinnedStage*
         if (rc)
             return rc;
         HIP_TRY(launch_totals(q.prec, a, s->M[0], s->stream));
+        // (the pass that counts the particles without a list)
+        if (q.lists)
+            HIP_TRY(launch_phase(PH_ROWSUM, q.dim, q.prec, a, s->stream));
         HIP_TRY(hipMemcpyAsync(&s->st->initial[0], &s->st->totals[0], sizeof(double) * 3,
                                hipMemcpyDeviceToDevice, s->stream));
     }
@@ -1171,6 +1187,11 @@ int create_into(mtpt_sim* s, const double* pos, const double* mass, PinnedStage*
     for (int c = 0; c < 3; ++c)
         s->mass_initial[c] = c < q.ns ? h.totals[c] : 0.0;
     s->mass_initial_known = true;
+    // crowded particles: the masks, in the same memory, with the same results
+    if (q.lists && (h.unlisted > static_cast<uint64_t>(q.n) / kListShare || h.most_pairs > kListCrowd)) {
+        s->q = make_plan(s->p, false);
+        carve(s);
+    }
     return MTPT_OK;
 }
 
