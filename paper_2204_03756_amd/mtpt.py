@@ -194,6 +194,22 @@ def current_stream_handle() -> int:
     return int(torch.cuda.current_stream().cuda_stream)
 
 
+# Allocators in use, by the handle whose library object calls into them until
+# it is destroyed (their callbacks are Python objects).
+_ALLOCATORS = {}
+
+
+def _keep(handle, allocator):
+    if allocator is not None:
+        _ALLOCATORS[handle.value] = allocator
+
+
+def _destroy(fn, handle):
+    value = handle.value if isinstance(handle, C.c_void_p) else handle
+    _check(fn(handle))
+    _ALLOCATORS.pop(value, None)
+
+
 # ------------------------------------------------------------ C entry points
 def mtpt_create(params, pos, mass, hip_stream=None, allocator: Optional[TorchAllocator] = None):
     lib = load()
@@ -205,6 +221,7 @@ def mtpt_create(params, pos, mass, hip_stream=None, allocator: Optional[TorchAll
                          C.c_void_p(hip_stream) if hip_stream else None,
                          C.byref(allocator.struct) if allocator is not None else None, C.byref(h))
     _check(rc)
+    _keep(h, allocator)
     return h
 
 
@@ -269,7 +286,7 @@ def mtpt_step_neighbors(sim, n: int, which: int):
 
 
 def mtpt_destroy(sim):
-    _check(load().mtpt_destroy(sim))
+    _destroy(load().mtpt_destroy, sim)
 
 
 def mtpt_set_profiling(sim, on: bool):
@@ -318,6 +335,7 @@ def mtpt_pool_create(hbm_budget: int, max_slots: int, hip_stream=None,
                                    C.c_void_p(hip_stream) if hip_stream else None,
                                    C.byref(allocator.struct) if allocator is not None else None,
                                    C.byref(h)))
+    _keep(h, allocator)
     return h
 
 
@@ -360,7 +378,7 @@ def mtpt_pool_usage(pool):
 
 
 def mtpt_pool_destroy(pool):
-    _check(load().mtpt_pool_destroy(pool))
+    _destroy(load().mtpt_pool_destroy, pool)
 
 
 # ------------------------------------------------------------ convenience
