@@ -208,7 +208,9 @@ int mtpt_step_neighbors(mtpt_sim* sim, int32_t which, int64_t* row_ptr, int64_t*
 
 /* Free the sim's device memory (and stream, if library-owned); the handle
  * is invalid afterwards.  NULL is a no-op.  Synchronises on the sim's
- * stream first. */
+ * stream first.  (The end of the last sim or pool gives back the pinned
+ * staging that exports of 64 MiB and more have left, at most 64 MiB, and then
+ * waits for the whole device.) */
 int mtpt_destroy(mtpt_sim* sim);
 
 /* Message of the last error on this thread ("" if none). */

@@ -91,6 +91,75 @@ void parallel_ranges(int64_t n, size_t bytes, F f)
 // bytes of a sim's inputs
 inline size_t input_bytes(const mtpt_params& p) { return static_cast<size_t>(p.n) * (p.dim + p.n_species) * 8; }
 
+// Pinned rings of large exports (copy_out).  hipHostFree waits for the whole
+// device, so none runs in an export: a ring is kept for the next one, of any sim
+// or pool, and given back when the last of those is destroyed.  At most kRings
+// exports at a time have one; the others copy without.
+constexpr size_t kCopyChunk = static_cast<size_t>(4) << 20;
+constexpr int kCopyRing = 8;
+constexpr int kRings = 2;
+
+class PinnedRings {
+    std::mutex mu;
+    char* idle[kRings] = {};
+    int n_idle = 0, made = 0;
+    int64_t handles = 0;
+
+public:
+    void born()
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        ++handles;
+    }
+    void gone()
+    {
+        char* back[kRings];
+        int n = 0;
+        {
+            std::lock_guard<std::mutex> lk(mu);
+            if (--handles > 0)
+                return;
+            for (; n_idle > 0; --made)
+                back[n++] = idle[--n_idle];
+        }
+        while (n > 0)
+            (void)hipHostFree(back[--n]);
+    }
+    // a ring for one export, or null
+    char* take()
+    {
+        {
+            std::lock_guard<std::mutex> lk(mu);
+            if (n_idle > 0)
+                return idle[--n_idle];
+            if (made == kRings)
+                return nullptr;
+            ++made;
+        }
+        void* p = nullptr;
+        if (hipHostMalloc(&p, kCopyRing * kCopyChunk, hipHostMallocPortable) == hipSuccess)
+            return static_cast<char*>(p);
+        (void)hipGetLastError();
+        std::lock_guard<std::mutex> lk(mu);
+        --made;
+        return nullptr;
+    }
+    void give(char* p)
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        idle[n_idle++] = p;
+    }
+};
+PinnedRings g_rings;
+
+// held by every sim and pool
+struct RingHandle {
+    RingHandle() { g_rings.born(); }
+    ~RingHandle() { g_rings.gone(); }
+    RingHandle(const RingHandle&) = delete;
+    RingHandle& operator=(const RingHandle&) = delete;
+};
+
 struct Alloc {
     mtpt_allocator a{};
     bool custom = false;
@@ -591,6 +660,7 @@ struct PhaseEv {
 }  // namespace
 
 struct mtpt_sim {
+    RingHandle rings;
     mtpt_params p{};
     Tensor tens;              // dispersion tensor (isotropic: tens.on == false)
     int device = 0;           // the HIP device current at create
@@ -915,24 +985,17 @@ int enqueue_step(mtpt_sim* s)
 }
 
 // Copies bytes of device memory to pageable host memory behind the work on
-// the sim's stream, and waits.  A large copy goes through a ring of pinned
-// chunks: this thread keeps the ring's copies in flight and makes every HIP
+// the sim's stream, and waits for that stream only.  A large copy goes through a
+// ring of pinned chunks: this thread keeps the ring's copies in flight and makes every HIP
 // call, and a few others write the chunks that have landed to the caller's
 // pages, first touches included.  One hipMemcpy stages through one thread
 // (768 MB into fresh pages 81 ms against 24 ms); below kCopyThreaded
 // allocating the ring costs more than that saves.
-constexpr size_t kCopyChunk = static_cast<size_t>(4) << 20;
 constexpr size_t kCopyThreaded = static_cast<size_t>(64) << 20;
-constexpr int kCopyRing = 8;
 
 hipError_t copy_out(mtpt_sim* s, void* out, const void* dev, size_t bytes)
 {
-    char* pinned = nullptr;
-    if (bytes >= kCopyThreaded &&
-        hipHostMalloc(reinterpret_cast<void**>(&pinned), kCopyRing * kCopyChunk, hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
-        pinned = nullptr;
-    }
+    char* const pinned = bytes >= kCopyThreaded ? g_rings.take() : nullptr;
     if (!pinned) {
         const hipError_t e = hipMemcpyAsync(out, dev, bytes, hipMemcpyDeviceToHost, s->stream);
         return e != hipSuccess ? e : hipStreamSynchronize(s->stream);
@@ -1021,7 +1084,7 @@ hipError_t copy_out(mtpt_sim* s, void* out, const void* dev, size_t bytes)
     for (hipEvent_t v : ev)
         if (v)
             (void)hipEventDestroy(v);
-    (void)hipHostFree(pinned);
+    g_rings.give(pinned);
     return e != hipSuccess ? e : es;
 }
 
@@ -1787,6 +1850,7 @@ struct RingSlot {
 }  // namespace
 
 struct mtpt_pool {
+    RingHandle rings;
     size_t budget = 0;
     size_t held = 0;
     int32_t max_slots = 1;
