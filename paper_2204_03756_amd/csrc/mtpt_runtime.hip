@@ -2011,14 +2011,16 @@ int mtpt_pool_create(size_t hbm_budget, int32_t max_slots, void* hip_stream, con
         }
         p->own_stream = true;
     }
-    if (hipStreamCreateWithFlags(&p->xstream, hipStreamNonBlocking) != hipSuccess ||
-        (p->own_stream && hipStreamCreateWithFlags(&p->stream3, hipStreamNonBlocking) != hipSuccess)) {
-        if (p->xstream)
-            (void)hipStreamDestroy(p->xstream);
+    if (hipStreamCreateWithFlags(&p->xstream, hipStreamNonBlocking) != hipSuccess) {
         if (p->own_stream)
             (void)hipStreamDestroy(p->stream);
         delete p;
         return fail(MTPT_E_DEVICE, "hipStreamCreateWithFlags failed");
+    }
+    // (without a second lane every sim runs on the one stream)
+    if (p->own_stream && hipStreamCreateWithFlags(&p->stream3, hipStreamNonBlocking) != hipSuccess) {
+        (void)hipGetLastError();
+        p->stream3 = nullptr;
     }
     *out = p;
     return MTPT_OK;

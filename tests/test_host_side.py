@@ -102,3 +102,25 @@ assert calls("hipHostMalloc") == 2 and a.shape == b.shape
 mtpt.mtpt_destroy(sim)
 assert calls("hipHostFree") == 1
 """, fail="hipHostMalloc:1")
+
+
+@pytest.mark.parametrize("failing,created", [(0, 1), (1, 0), (2, 0), (3, 1)])
+def test_a_pool_needs_two_streams_and_takes_a_third(fakehip, failing, created):
+    """The third stream, the 3-d sims' lane, is not needed: without it the pool
+    steps every sim on the first.  Every stream made is destroyed."""
+    _run(fakehip, f"""
+try:
+    pool = mtpt.mtpt_pool_create(1 << 30, 4)
+except mtpt.MtptError as e:
+    assert not {created} and e.code == mtpt.MTPT_E_DEVICE
+else:
+    assert {created}
+    n = 1000
+    t = [mtpt.mtpt_pool_admit(pool, params(n, dim=d), np.full((n, d), 0.5), np.ones((1, n)), 2) for d in (2, 3, 2, 3)]
+    assert [mtpt.mtpt_pool_tick(pool) for _ in range(2)] == [0, 4]
+    assert all(mtpt.mtpt_pool_done(pool, k) for k in t)
+    for k in t:
+        mtpt.mtpt_pool_result(pool, k, n, 1)
+    mtpt.mtpt_pool_destroy(pool)
+assert calls("hipStreamDestroy") == calls("hipStreamCreateWithFlags") - {1 if failing else 0}
+""", fail=f"hipStreamCreateWithFlags:{failing}" if failing else None)
