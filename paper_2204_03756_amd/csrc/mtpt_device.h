@@ -780,28 +780,35 @@ __device__ __forceinline__ V lds_at(const V* base, int off)
 }
 
 // Cutoff test of one candidate per lane, as a lane mask in scalar registers.
-// FP64: exact.  FP32: r2 <= psi2_out, and band collects the lanes whose r2
-// lies in the band in which only the FP64 test decides (the caller then
-// repeats its chunk with Metric::inside).
-__device__ __forceinline__ uint64_t within(const SimArgs& a, double r2, uint64_t valid, uint64_t&)
+// FP64: exact.  FP32: r2 <= psi2_out; in_band, the lanes whose r2 lies in the
+// band in which only the FP64 test decides (the caller then repeats its chunk
+// with Metric::inside).
+__device__ __forceinline__ uint64_t within(const SimArgs& a, double r2)
 {
-    return __builtin_amdgcn_fcmp(r2, a.psi2, kFcmpLe) & valid;
+    return __builtin_amdgcn_fcmp(r2, a.psi2, kFcmpLe);
 }
-__device__ __forceinline__ uint64_t within(const SimArgs& a, float r2, uint64_t valid, uint64_t& band)
+__device__ __forceinline__ uint64_t within(const SimArgs& a, float r2)
 {
-    const uint64_t in = __builtin_amdgcn_fcmpf(r2, a.psi2_out, kFcmpLe) & valid;
-    band |= __builtin_amdgcn_fcmpf(r2, a.psi2_in, kFcmpGe) & in;
-    return in;
+    return __builtin_amdgcn_fcmpf(r2, a.psi2_out, kFcmpLe);
 }
-// 2 w + this lane's bit of the lane mask in: one add with the mask as its
-// carry-in (the compiler takes a select, a shift and an or).  in must come
-// from a scalar instruction (here: the and with the valid mask), which the
-// hardware orders before a vector instruction that reads it.
-__device__ __forceinline__ uint32_t shift_in(uint32_t w, uint64_t in)
+__device__ __forceinline__ uint64_t in_band(const SimArgs&, double) { return 0ull; }
+__device__ __forceinline__ uint64_t in_band(const SimArgs& a, float r2)
+{
+    return __builtin_amdgcn_fcmpf(r2, a.psi2_in, kFcmpGe);
+}
+// in = near & valid, and 2 w + this lane's bit of it: one add with the mask as
+// its carry-in (the compiler takes a select, a shift and an or).  The scalar and
+// stands in the same block: a vector instruction may not read a mask that a
+// compare has just written, and the compiler does not look into the block to
+// keep them apart, but the hardware orders it behind a scalar one.
+__device__ __forceinline__ uint32_t shift_in(uint32_t w, uint64_t near, uint64_t valid, uint64_t& in)
 {
     uint32_t r;
     uint64_t carry_out;
-    asm("v_addc_co_u32_e64 %0, %1, %2, %2, %3" : "=v"(r), "=s"(carry_out) : "v"(w), "s"(in));
+    asm("s_and_b64 %0, %3, %4\n\tv_addc_co_u32_e64 %1, %2, %5, %5, %0"
+        : "=s"(in), "=v"(r), "=s"(carry_out)
+        : "s"(near), "s"(valid), "v"(w)
+        : "scc");
     return r;
 }
 
@@ -1636,10 +1643,10 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
 #pragma unroll
                         for (int u = 0; u < U; ++u) {
                             const T r2 = Metric<D, T, TN>::r2(a, xi, xj[u]);
-                            const uint64_t in =
-                                within(a, r2, __builtin_amdgcn_uicmp(k + u, tot, kIcmpUlt), band);
+                            uint64_t in;
+                            mw = shift_in(mw, within(a, r2), __builtin_amdgcn_uicmp(k + u, tot, kIcmpUlt), in);
+                            band |= in_band(a, r2) & in;
                             visit(off[u], __builtin_amdgcn_inverse_ballot_w64(in), r2);
-                            mw = shift_in(mw, in);
                         }
                     };
                     // one candidate, with the exact test

@@ -147,10 +147,10 @@ __device__ __forceinline__ void list_rowsum(const SimArgs& a, const double (*lpo
                 for (int d = 0; d < 3; ++d)
                     xj[u][d] = lds_at(lpos[d], static_cast<int>(off[u]));
             }
-            uint64_t in[U], unused = 0;
+            uint64_t in[U];
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                in[u] = within(a, Pair<3, double>::r2(xi, xj[u]), __builtin_amdgcn_uicmp(k + u, tot, kIcmpUlt), unused);
+                in[u] = within(a, Pair<3, double>::r2(xi, xj[u])) & __builtin_amdgcn_uicmp(k + u, tot, kIcmpUlt);
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (__builtin_amdgcn_inverse_ballot_w64(in[u])) {
