@@ -920,6 +920,10 @@ __device__ __forceinline__ uint32_t bin_next(const SimArgs& a, uint32_t i, const
     return rank;
 }
 
+}  // namespace mtpt
+#include "mtpt_lists.h"
+namespace mtpt {
+
 // One tile: tx * ty * tz cells (tz = 1 in 2-d).  Halo rows (cells xa..xb-1
 // of rows y0-1..y1 of planes z0-1..z1) are staged in LDS with the offsets of
 // their cell boundaries; a particle in cell cx visits cells cx-1..cx+1 of
@@ -930,10 +934,7 @@ __device__ __forceinline__ uint32_t bin_next(const SimArgs& a, uint32_t i, const
 // the pairs it would use -- a.nb_col == nullptr: their count plus one (self)
 // into a.nb_cnt[pid]; else the pids, self first, into a.nb_col from
 // a.nb_row[pid] -- and skips every store of the step.
-}  // namespace mtpt
-#include "mtpt_lists.h"
-namespace mtpt {
-
+// With LIST the tile is that of mtpt_lists.h, for kListBlock threads.
 template <int D, int PREC, int NS, bool TRANSFER, bool TN, bool EXPORT = false, bool LIST = false>
 __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
 {
@@ -1158,7 +1159,7 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
     }
     if (use_lds) {
         // Each halo row is one contiguous run in HBM and in LDS.  A thread
-        // stages slots tid, tid + kBlock, ...: it finds every slot's row
+        // stages slots tid, tid + NT, ...: it finds every slot's row
         // first (the searches advance together), then issues all its loads,
         // then all its LDS stores, so that its loads are in flight at once.
         constexpr int kIt = (CAP + NT - 1) / NT;
@@ -1671,16 +1672,12 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
                     } else {
                         constexpr int kGroup = D == 3 ? MTPT_ROW_GROUP_3D
                                                       : (PREC == 0 ? MTPT_ROW_GROUP_2D_F64 : MTPT_ROW_GROUP_2D);
+                        static_assert(kGroup <= 4, "the rest of a chunk is done by twos and ones");
                         const auto before = acc;
                         uint64_t band = 0ull;
                         uint32_t k = k0;
                         for (; k + kGroup <= kend; k += kGroup)
                             group(std::integral_constant<int, kGroup>{}, k, band);
-                        if constexpr (kGroup > 4)
-                            if (k + 4 <= kend) {
-                                group(std::integral_constant<int, 4>{}, k, band);
-                                k += 4;
-                            }
                         if constexpr (kGroup > 2)
                             if (k + 2 <= kend) {
                                 group(std::integral_constant<int, 2>{}, k, band);
@@ -1997,7 +1994,10 @@ __device__ __forceinline__ const SimArgs& kernel_args()
 template <int D, int PREC, bool TN>
 __global__ __launch_bounds__(kBlock, D == 3 && PREC == 1 && !TN ? 7 : 1) void rowsum_k(SimArgs a)
 {
-    // (ellipsoidal cutoff: by value, 23.6 us against 24.1 at 5e5 particles in 2-d)
+    // (ellipsoidal cutoff: by value.  By value / through the constant address
+    // space, us a launch: 2-d FP32W 1e4 10.4 / 10.7, 5e4 12.2 / 12.3, 5e5 24.6 / 24.7,
+    // 2e6 53.2 / 52.2, FP64 2e6 95.7 / 94.9; 3-d 5e4 to 1e6 within 1 % both ways.  A
+    // whole step of 1e4 takes 30.3 / 32.0, of 5e4 33.7 / 35.4.)
     tile_body<D, PREC, 1, false, TN>(TN ? a : kernel_args(), xcd_block(blockIdx.x, gridDim.x));
 }
 template <int D, int PREC, bool TN>

@@ -102,8 +102,9 @@ template <int D, int PREC, int NS> struct LdsBudget {
 
 // candidates of the row-sum pass's loop whose LDS reads are issued together
 // (measured, us a launch for 1, 2, 3, 4 of the 4e6-particle 2-d pass: 90, 83,
-// 84, 86; for 2, 4, 6, 8 of the 1e5-particle 3-d one: 48, 45, 43, 43, and of
-// the 2e6-particle one: 244, 245, 242, 248)
+// 84, 86; in FP64 of 1e6: 54.9, 52.3, 52.7, 51.7, of 1e4: 14.8, 13.3, 13.1, 13.0; for
+// 2 and 4 of the 1e5-particle 3-d one: 48, 45, and of the 2e6-particle one: 244,
+// 245, longer groups within 2 %)
 #ifndef MTPT_ROW_GROUP_2D
 #define MTPT_ROW_GROUP_2D 2
 #endif
