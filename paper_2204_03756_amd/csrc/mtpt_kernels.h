@@ -116,7 +116,7 @@ template <int D, int PREC, int NS> struct LdsBudget {
 #endif
 
 // Neighbour-list variant of the 3-d FP64 passes (mtpt_lists.h): threads of a
-// workgroup (one pass over a tile of about 410 particles), particles a tile
+// workgroup (one pass over a tile of about 430 particles), particles a tile
 // stages (positions, row sums and three species: two workgroups per CU),
 // words and entries of a packed list, its count when a particle has none, and
 // rows of the row-sum pass's lists in LDS (a group of four past the end)
@@ -125,8 +125,8 @@ constexpr int kListCap = 1330;
 constexpr int kListWords = 7;
 constexpr int kListMax = 2 + 3 * (kListWords - 1);
 constexpr uint32_t kListNone = 63u;
-constexpr int kListWhole = 3;       // SimArgs::lsplit of tiles that are one transfer tile
 constexpr int kListDepth = kListMax + 1 + 4;
+constexpr int kListWhole = 3;   // SimArgs::lsplit of tiles that are one transfer tile
 
 // Largest tile (cells in x, y and z) of the mass-transfer passes, the halo
 // cell rows it spans and the cell boundaries kept per halo row.  Halo rows

@@ -523,8 +523,9 @@ Plan make_plan(const mtpt_params& p, bool lists)
         // neighbours fit a list, 4.5 standard deviations above their mean
         // included, with tiles that fill half a workgroup, of which there are
         // min_tiles: with fewer a launch lasts as long as its largest tile
-        // (reacting workload, us a step mask / list: 2e5 particles 100 / 88, 1e6
-        // 274 / 229, 4e6 969 / 867).  A list tile is one transfer tile or two
+        // (reacting workload, us a step mask / list: 1e5 particles 80 / 67, 4e5 144 /
+        // 113, 1e6 269 / 225, 8e6 1883 / 1644; one species of 5.6 neighbours 4e5 131 /
+        // 106, 2e6 463 / 432).  A list tile is one transfer tile or two
         // along an axis.  Of the shapes that suit the mask variant as well as
         // the one chosen above (as few tiles, as much room for a denser place:
         // with 12 % larger halos and 25 % more particles than the mean in a
