@@ -962,7 +962,8 @@ __device__ __forceinline__ void tile_body(const SimArgs& a, uint32_t blk)
     using M = typename Types<PREC>::M;
     static_assert(!LIST || (D == 3 && PREC == 0 && !TN), "neighbour lists: 3-d, FP64, isotropic");
     constexpr int NT = LIST ? kListBlock : kBlock;
-    constexpr int CAP = LIST ? kListCap : TileCap<D, PREC, NS, TRANSFER>::value;
+    constexpr int CAP = LIST ? kListCap
+                             : TileCap<D, PREC, NS, TRANSFER>::value + (D == 3 && PREC == 0 && NS == 3 && !TN ? kSpareCap : 0);
     constexpr int planes = D == 3 ? 3 : 1;
     constexpr int SCAP = TRANSFER ? CAP : 1;
     // rows are trimmed to the spherical cutoff's x-window; an ellipsoidal

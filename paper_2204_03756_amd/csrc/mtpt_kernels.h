@@ -115,6 +115,14 @@ template <int D, int PREC, int NS> struct LdsBudget {
 #define MTPT_ROW_GROUP_3D 4
 #endif
 
+// 3-d FP64 three-species transfer pass: particles a tile may stage beyond the
+// capacity its shape is chosen for, so that the shapes that suit neighbour lists
+// (9 x 6 x 3 cells beside 6 x 5 x 5) have room where the particles are denser
+// than their mean.  They take its LDS to 53712 bytes, the most of which a CU
+// holds three workgroups: with 40 (54160 bytes, two) the pass took 122 us instead
+// of 98 at 1e6 evenly spread particles.
+constexpr int kSpareCap = 32;
+
 // Neighbour-list variant of the 3-d FP64 passes (mtpt_lists.h): threads of a
 // workgroup (one pass over a tile of about 430 particles), particles a tile
 // stages (positions, row sums and three species: two workgroups per CU),
@@ -299,8 +307,9 @@ uint32_t phase_blocks(int ph, const SimArgs& a);
 
 // single-sim launch of a phase
 hipError_t launch_phase(int ph, int dim, int prec, const SimArgs& a, hipStream_t s);
-// PH_PLACE of a, with the PH_FINALIZE of the previous step prev run by one
-// more workgroup of the same launch
+// PH_SCATTER or PH_PLACE of a, with the PH_FINALIZE of the previous step prev run
+// by one more workgroup of the same launch
+hipError_t launch_scatter_fin(const SimArgs& a, const SimArgs& prev, hipStream_t s);
 hipError_t launch_place_fin(int dim, int prec, const SimArgs& a, const SimArgs& prev, hipStream_t s);
 // batched launch of a phase over sims that share (dim, prec, ns, tensor)
 hipError_t launch_phase_batched(int ph, int dim, int prec, int ns, int tn, const Batch& b, hipStream_t s);

@@ -43,8 +43,17 @@ __global__ __launch_bounds__(kBlock) void place_kb(Batch b)
     place_body<D, typename Types<PREC>::T, typename Types<PREC>::M>(a, l);
 }
 
-// place_k with one more workgroup, the first, that finalizes the previous
-// step (its totals and pair counters) while the gathers run
+// place_k, or scatter_k where the partial sums lie in the spare pids, with one
+// more workgroup, the first, that finalizes the previous step (its totals and
+// pair counters) while the gathers run
+__global__ __launch_bounds__(kBlock) void scatter_fin_k(SimArgs a, SimArgs prev)
+{
+    if (blockIdx.x == 0) {
+        finalize_body<kBlock>(prev, prev.partials, prev.recompute_s != 0, prev.nttiles, 0);
+        return;
+    }
+    scatter_body(a, xcd_block(blockIdx.x - 1, gridDim.x - 1));
+}
 template <int D, int PREC>
 __global__ __launch_bounds__(kBlock) void place_fin_k(SimArgs a, SimArgs prev)
 {
@@ -320,6 +329,12 @@ hipError_t launch_phase(int ph, int dim, int prec, const SimArgs& a, hipStream_t
     case PH_FINALIZE: finalize_k<<<1, kFinalBlock, 0, s>>>(a, a.nttiles, 0); break;
     default: return hipErrorInvalidValue;
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_scatter_fin(const SimArgs& a, const SimArgs& prev, hipStream_t s)
+{
+    scatter_fin_k<<<phase_blocks(PH_SCATTER, a) + 1, kBlock, 0, s>>>(a, prev);
     return hipGetLastError();
 }
 

@@ -204,6 +204,7 @@ struct Plan {
     uint32_t ttiles_x = 1, ttiles_y = 1, nttiles = 0;
     bool lists = false;                       // neighbour lists: tile is both passes' tile, of one
     int lsplit = kListWhole;                  // transfer tile or two along this axis
+    bool sums_in_pids = false;                // partial sums of a step: in the spare pid buffer
     bool trim_rows = false;
     bool tensor = false;
     size_t tsz = 8, msz = 8;
@@ -415,12 +416,10 @@ Plan make_plan(const mtpt_params& p, bool lists)
     // cell): its step time is then the time of one small tile, not that of a
     // few large tiles on a mostly idle chip.
     size_t room_part = 0, room_pair = 0;
-    // bytes of the workgroups' sums: of the set-up totals and of a step, of a
-    // step alone
+    // bytes of the workgroups' sums: of the set-up totals and of a step
     auto part_bytes = [&]() {
         return align_up(static_cast<size_t>(std::max(q.part_blocks, q.nttiles)) * q.ns * 8, 256);
     };
-    auto step_bytes = [&]() { return static_cast<size_t>(q.nttiles) * q.ns * 8; };
     {
         const double rho_c = static_cast<double>(q.n) / static_cast<double>(q.ncells);
         const int64_t min_tiles = tile_min_tiles();
@@ -523,18 +522,18 @@ Plan make_plan(const mtpt_params& p, bool lists)
         // neighbours fit a list, 4.5 standard deviations above their mean
         // included, with tiles that fill half a workgroup, of which there are
         // min_tiles: with fewer a launch lasts as long as its largest tile
-        // (reacting workload, us a step mask / list: 1e5 particles 80 / 67, 4e5 144 /
-        // 113, 1e6 269 / 225, 8e6 1883 / 1644; one species of 5.6 neighbours 4e5 131 /
-        // 106, 2e6 463 / 432).  A list tile is one transfer tile or two
-        // along an axis.  Of the shapes that suit the mask variant as well as
-        // the one chosen above (as few tiles, as much room for a denser place:
-        // with 12 % larger halos and 25 % more particles than the mean in a
-        // place its 1e6-particle step took 395 us instead of 314), the pair with
-        // the least estimated list cost is taken, by the mask variant too, so
-        // that both leave the same partial sums.  Tiles of 11 x 6 x 5 cells, not
-        // two of anything, were 4 % faster at 8e6 particles, 1 % at 1e6.  Sims that
-        // a drift gathers at the walls keep the masks, as do those whose
-        // particles are found crowded at create (kListShare).
+        // (reacting workload, us a step mask / list: 1e5 particles 79 / 67, 4e5 143 /
+        // 115, 1e6 264 / 216, 8e6 1805 / 1593; one species of 5.6 neighbours 4e5 127 /
+        // 104).  A list tile is one transfer tile or two along an axis.  Of the
+        // shapes that suit the mask variant about as well as the one chosen above
+        // (as few tiles, halos up to 13 % larger that leave room for particles a
+        // quarter denser than their mean), the pair with the least estimated list
+        // cost is taken, by the mask variant too, so that both leave the same
+        // partial sums.  With halos no larger than that one's the tiles of 1e6
+        // particles were halves of 10 x 5 x 5 cells instead of 9 x 6 x 6: lists 230 us
+        // instead of 216, 2e7 particles 4189 instead of 3907.  Sims that a drift
+        // gathers at the walls keep the masks, as do those whose particles are
+        // found crowded at create (kListShare).
         if (q.dim == 3 && q.prec == MTPT_FP64 && !q.tensor && !q.trim_rows) {
             double side3 = 1.0;
             for (int k = 0; k < 3; ++k)
@@ -542,52 +541,50 @@ Plan make_plan(const mtpt_params& p, bool lists)
             const double mean = rho_c / side3 * 4.18879 * q.psi * q.psi * q.psi;
             auto own_of = [&](const int* t) { return t[0] * t[1] * static_cast<double>(t[2]) * rho_c; };
             auto halo_of = [&](const int* t) { return (t[0] + 2.0) * (t[1] + 2.0) * (t[2] + 2.0) * rho_c; };
-            const double halo_max = halo_of(q.ttile);
+            const double halo_max = std::min(1.13 * halo_of(q.ttile), tile_capacity(3, q.prec, q.ns) / 1.25);
             const bool drift = p.vel[0] != 0.0 || p.vel[1] != 0.0 || p.vel[2] != 0.0;
             double best = 0.0;
             int tt[3] = {1, 1, 1}, lt[3] = {1, 1, 1};
             uint32_t lx = 0, ly = 0;
-            for (int z = 1; z <= std::min(q.nc[2], tile_max(3, 2)); ++z)
-                for (int y = 1; y <= std::min(q.nc[1], tile_max(3, 1)); ++y)
-                    for (int x = 1; x <= std::min(q.nc[0], tile_max(3, 0)); ++x) {
-                        const int t[3] = {x, y, z};
-                        const double sub = own_of(t);
-                        if (halo_of(t) > halo_max || count(t, &lx, &ly) > q.nttiles)
-                            continue;
-                        for (int axis = 0; axis <= kListWhole; ++axis) {
-                            int l[3] = {x, y, z};
-                            if (axis < kListWhole)
-                                l[axis] *= 2;
-                            const double own = own_of(l), halo = halo_of(l);
-                            if (axis < kListWhole && (l[axis] > tile_max(3, axis) || t[axis] >= q.nc[axis] ||
-                                                      sub + 2.0 * std::sqrt(sub) > kBlock))
+            // (as many transfer tiles as chosen above at most, else 8 % or 17 %
+            // more: where those are eight cells wide, and two are beyond the limits)
+            for (double most = q.nttiles; best == 0.0 && most < 1.2 * q.nttiles; most *= 1.08)
+                for (int z = 1; z <= std::min(q.nc[2], tile_max(3, 2)); ++z)
+                    for (int y = 1; y <= std::min(q.nc[1], tile_max(3, 1)); ++y)
+                        for (int x = 1; x <= std::min(q.nc[0], tile_max(3, 0)); ++x) {
+                            const int t[3] = {x, y, z};
+                            const double sub = own_of(t);
+                            if (halo_of(t) > halo_max || count(t, &lx, &ly) > most)
                                 continue;
-                            if (halo * 1.25 > kListCap || own + 2.0 * std::sqrt(own) > kListBlock || own < kListBlock / 2)
-                                continue;
-                            const uint32_t nl = count(l, &lx, &ly);
-                            const double cost = nl * (64.0 * std::ceil(own / 64.0 + 0.5) + 0.1 * halo);
-                            if (nl < min_tiles)
-                                continue;
-                            if (best == 0.0 || cost < best) {
-                                best = cost;
-                                q.lsplit = axis;
-                                std::copy(t, t + 3, tt);
-                                std::copy(l, l + 3, lt);
+                            for (int axis = 0; axis <= kListWhole; ++axis) {
+                                int l[3] = {x, y, z};
+                                if (axis < kListWhole)
+                                    l[axis] *= 2;
+                                const double own = own_of(l), halo = halo_of(l);
+                                if (axis < kListWhole && (l[axis] > tile_max(3, axis) || t[axis] >= q.nc[axis] ||
+                                                          sub + 1.5 * std::sqrt(sub) > kBlock))
+                                    continue;
+                                if (halo * 1.25 > kListCap || own + 2.0 * std::sqrt(own) > kListBlock || own < kListBlock / 2)
+                                    continue;
+                                const uint32_t nl = count(l, &lx, &ly);
+                                const double cost = nl * (64.0 * std::ceil(own / 64.0 + 0.5) + 0.1 * halo);
+                                if (nl < min_tiles)
+                                    continue;
+                                if (best == 0.0 || cost < best) {
+                                    best = cost;
+                                    q.lsplit = axis;
+                                    std::copy(t, t + 3, tt);
+                                    std::copy(l, l + 3, lt);
+                                }
                             }
                         }
-                    }
-            const uint32_t nlist = count(lt, &lx, &ly);
-            // (the sim's memory is laid out for the mask variants' tiles)
-            const bool fits = step_bytes() + nlist * 4u <= room_part + room_pair;
-            if (best > 0.0 && 1.0 + mean + 4.5 * std::sqrt(mean) <= kListMax && fits) {
+            if (best > 0.0 && 1.0 + mean + 4.5 * std::sqrt(mean) <= kListMax) {
                 std::copy(tt, tt + 3, q.ttile);
                 q.nttiles = count(q.ttile, &q.ttiles_x, &q.ttiles_y);
                 if (lists && !drift) {
                     q.lists = true;
                     std::copy(lt, lt + 3, q.tile);
-                    q.tiles_x = lx;
-                    q.tiles_y = ly;
-                    q.ntiles = nlist;
+                    q.ntiles = count(q.tile, &q.tiles_x, &q.tiles_y);
                 }
             }
         }
@@ -624,9 +621,20 @@ Plan make_plan(const mtpt_params& p, bool lists)
     q.off_bsum = take(static_cast<size_t>(q.scan_blocks) * 4);
     q.off_part = take(room_part);
     q.off_pair = take(room_pair);
-    const size_t sums = q.lists ? step_bytes() : part_bytes();
-    if (sums > room_part || q.ntiles * 4u > room_pair)
-        q.off_pair = q.off_part + sums;
+    // A sim's memory is laid out for the shapes in waves.  More pair counts than
+    // those have room for lie behind the mass sums; sums that leave them no room
+    // there lie in the pid buffer that is free between a step's place pass and the
+    // next one's (a static sim's second one), and the scatter launch before that
+    // finalizes the step.
+    const size_t sums = q.lists ? static_cast<size_t>(q.nttiles) * q.ns * 8 : part_bytes();
+    const size_t pairs = static_cast<size_t>(q.ntiles) * 4;
+    if (sums > room_part || pairs > room_pair) {
+        q.sums_in_pids = sums + pairs > room_part + room_pair;
+        if (!q.sums_in_pids)
+            q.off_pair = q.off_part + sums;
+        else if (pairs > room_pair)
+            q.off_pair = q.off_part;
+    }
     q.off_stats = take(sizeof(DevStats));
     q.bytes = off;
     return q;
@@ -867,6 +875,8 @@ SimArgs step_args(const mtpt_sim* s, bool* rowsum_needed)
             a.m_dst[c] = s->M[0][c];
         }
         a.recompute_s = 1;
+        if (s->q.sums_in_pids)
+            a.partials = reinterpret_cast<double*>(s->P[t & 1]);
         // the row-sum pass (run every step of a moving sim) moves the three
         // species' masses instead of the place pass (measured on the 3.2e7-
         // particle reacting workload: place 0.92 -> 0.64 ms, row-sum 1.27 ->
@@ -884,6 +894,8 @@ SimArgs step_args(const mtpt_sim* s, bool* rowsum_needed)
         a.recompute_s = s->s_valid ? 0 : 1;
         if ((t & 1) && s->partials_odd)
             a.partials = s->partials_odd;
+        else if (s->q.sums_in_pids)
+            a.partials = reinterpret_cast<double*>(s->P[1]);
     }
     a.fuse_bin = s->moving ? 1 : 0;
     a.tcounts_valid = (s->moving && s->bin_ready) ? 1 : 0;
@@ -891,8 +903,8 @@ SimArgs step_args(const mtpt_sim* s, bool* rowsum_needed)
     return a;
 }
 
-// Launch one phase of a sim; with prev (PH_PLACE only) the same launch also
-// finalizes the step that prev describes.
+// Launch one phase of a sim; with prev (PH_SCATTER and PH_PLACE only) the same
+// launch also finalizes the step that prev describes.
 int launch(mtpt_sim* s, int ph, const SimArgs& a, const SimArgs* prev = nullptr)
 {
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -901,7 +913,9 @@ int launch(mtpt_sim* s, int ph, const SimArgs& a, const SimArgs* prev = nullptr)
         HIP_TRY(hipEventCreate(&e1));
         HIP_TRY(hipEventRecord(e0, s->stream));
     }
-    if (prev)
+    if (prev && ph == PH_SCATTER)
+        HIP_TRY(launch_scatter_fin(a, *prev, s->stream));
+    else if (prev)
         HIP_TRY(launch_place_fin(s->q.dim, s->q.prec, a, *prev, s->stream));
     else
         HIP_TRY(launch_phase(ph, s->q.dim, s->q.prec, a, s->stream));
@@ -923,8 +937,9 @@ int flush_finalize(mtpt_sim* s)
 
 // Binning; the bin phase itself is skipped when the previous transfer pass
 // already walked and binned every particle for this step.  With prev, the
-// place launch also finalizes the step that prev describes (before this
-// step's row-sum and transfer passes rewrite its partial sums).
+// place launch (the scatter launch where the place pass writes over its partial
+// sums) also finalizes the step that prev describes, before this step's row-sum
+// and transfer passes rewrite them.
 int enqueue_binning(mtpt_sim* s, const SimArgs& a, bool with_bin, const SimArgs* prev = nullptr)
 {
     static const int phases[] = {PH_BIN, PH_SCAN_REDUCE, PH_SCAN_TOP, PH_SCAN_DOWN,
@@ -934,7 +949,7 @@ int enqueue_binning(mtpt_sim* s, const SimArgs& a, bool with_bin, const SimArgs*
             continue;
         if (ph == PH_SCAN_TOP && a.scan_fold)
             continue;
-        const int rc = launch(s, ph, a, ph == PH_PLACE ? prev : nullptr);
+        const int rc = launch(s, ph, a, ph == (s->q.sums_in_pids ? PH_SCATTER : PH_PLACE) ? prev : nullptr);
         if (rc)
             return rc;
     }

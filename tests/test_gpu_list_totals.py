@@ -9,7 +9,7 @@ from paper_2204_03756_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
-from gpu_helpers import load_mt, say  # noqa: E402
+from gpu_helpers import TOL, load_mt, normwise, say  # noqa: E402
 
 
 @pytest.fixture(scope="module")
@@ -18,8 +18,9 @@ def mt():
 
 
 # (particles, box, species, axis of the two transfer tiles (None: one), particles in the first tile's cells)
-CASES = [(899, [18.1, 5.3, 13.1], 1, 0, 0), (9001, [20.8, 20.8, 20.8], 3, 0, 0), (1411, [8.8, 12.6, 22.8], 3, 0, 420),
-         (1189, [14.7, 10.7, 8.0], 1, 1, 0), (1267, [19.0, 5.2, 15.0], 3, 1, 0), (1155, [8.4, 16.9, 10.2], 1, 2, 0),
+CASES = [(995, [18.3, 7.0, 18.0], 1, 0, 0), (9001, [20.8, 20.8, 20.8], 3, 0, 0), (1411, [8.8, 12.6, 22.8], 3, 0, 420),
+         (1303, [21.4, 11.0, 11.9], 1, 1, 0), (1267, [19.0, 5.2, 15.0], 3, 1, 0), (1155, [8.4, 16.9, 10.2], 1, 2, 0),
+         (2993, [16.2, 22.3, 18.0], 3, 0, 0), (27427, [29.2, 35.2, 35.7], 3, 0, 0), (15667, [16.6, 23.9, 43.0], 3, None, 0),
          (1189, [8.8, 7.2, 23.5], 3, 2, 0), (1051, [20.4, 7.1, 10.6], 1, None, 0), (1101, [13.3, 15.8, 11.6], 3, None, 560)]
 
 
@@ -52,3 +53,45 @@ def test_totals_alone_equal_the_pools(mt, monkeypatch, n, hi, ns, axis, first, d
     finally:
         mt.mtpt_pool_destroy(pool)
     assert pooled == alone
+
+
+@pytest.mark.parametrize("d_rw", [0.3, 0.0])
+@pytest.mark.parametrize("plume", [False, True])
+def test_sums_that_the_ordinary_place_has_no_room_for(mt, oracle, monkeypatch, plume, d_rw):
+    """Partial sums in the pid buffer that is free between two place passes (a
+    static sim's second one), finalized by the scatter launch: with lists and,
+    where the particles crowd together, with masks, alone and in a pool, read
+    after every step and at the end only."""
+    monkeypatch.setenv("MTPT_MIN_TILES", "1")
+    rng = np.random.Generator(np.random.Philox(20230123))
+    n, hi, psi = 27427, np.array([29.2, 35.2, 35.7]), 1.1
+    p = W.Params(dim=3, n=n, lo=[0.0] * 3, hi=list(hi), d_rw=d_rw, d_mt=psi * psi / 3.6, dt=0.1, psi=psi, seed=6,
+                 n_species=3, k_react=1.0, precision=W.FP64)
+    x, m = rng.random((n, 3)) * hi, rng.random((3, n))
+    if plume:
+        x = np.clip(hi / 2 + hi / 6 * rng.standard_normal((n, 3)), 0.0, hi)
+    say(f"  sums in the spare pids plume={plume} d_rw={d_rw}")
+    alloc = mt.TorchAllocator("cuda:0")
+    got = []
+    for chunks in ([1] * 6, [6], [2, 3, 1]):
+        with mt.Sim(p, x, m, allocator=alloc) as sim:
+            assert mt.mtpt_sim_plan(sim.h)["lists"] != plume
+            for k in chunks:
+                sim.step(k)
+                st = sim.stats()
+            got.append((st, sim.masses(), sim.positions()))
+    pool = mt.mtpt_pool_create(0, 1, None, alloc)
+    try:
+        t = mt.mtpt_pool_admit(pool, p, x, m, 6)
+        for _ in range(6):
+            mt.mtpt_pool_tick(pool)
+        pooled = mt.mtpt_pool_stats(pool, t)
+        assert np.array_equal(mt.mtpt_pool_result(pool, t, n, 3), got[0][1])
+    finally:
+        mt.mtpt_pool_destroy(pool)
+    ref = oracle.run(p, x, m, 6)
+    for st, masses, pos in got:
+        assert st == pooled and st["pairs_total"] == int(ref.pairs.sum())
+        assert np.array_equal(masses, got[0][1]) and np.array_equal(pos, ref.x)
+        assert normwise(masses, ref.m) <= TOL[W.FP64]
+        assert np.all(np.abs(np.array(st["mass_total"]) - ref.totals[-1]) <= TOL[W.FP64] * ref.totals[-1])

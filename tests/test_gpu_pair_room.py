@@ -19,7 +19,7 @@ def mt():
 
 # (particles, per unit of volume, species, precision, row-sum tiles, transfer tiles, lists); in
 # waves of particles the row-sum tiles were 256, 320, 256, 256 and 280
-CASES = [(63_709, 0.5, 1, W.FP64, 400, 400, False), (63_709, 1.0, 3, W.FP64, 400, 360, False),
+CASES = [(63_709, 1.0, 1, W.FP64, 400, 400, False), (63_709, 1.0, 3, W.FP64, 400, 360, False),
          (63_709, 1.0, 3, W.FP32W_FP64ACC, 400, 360, False), (75_177, 1.0, 1, W.FP32_KAHAN, 264, 264, False),
          (75_177, 0.5, 3, W.FP64, 336, 336, True)]
 

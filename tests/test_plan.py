@@ -50,3 +50,12 @@ def test_list_tiles_are_doubled_inside_the_grid_only(n, hi, ns, monkeypatch):
     for axis in range(3):
         if plan["lists"] and plan["tile"][axis] != plan["ttile"][axis]:
             assert plan["ttile"][axis] < int(hi[axis] / (1.1 * (1 + 1e-6))), plan
+
+
+@pytest.mark.parametrize("n", [200_003, 221_717, 443_990, 1_000_001, 1_727_426, 2_256_415, 8_000_000, 20_000_000, 32_000_000])
+def test_reacting_sims_of_every_size_take_lists(n):
+    """The reacting workload's density: also where the transfer pass's best tile
+    is eight cells wide, whose double reaches past the mask variant's limit."""
+    plan = mtpt.mtpt_plan(_cube(n, 32e6 / 318.0 ** 3, 3, W.FP64, 0.7, 0.05))
+    assert plan["lists"], plan
+    assert plan["tile"][0] * plan["tile"][1] * plan["tile"][2] <= 12 * 6 * 6
