@@ -14,8 +14,8 @@
 // For that both passes stage the same tiles in the same order, in workgroups
 // of kListBlock threads (two per CU by LDS).  Both passes are bound by VALU
 // issue and by the latency of their setup.  Reacting workload, row-sum and
-// transfer launch, mask and list variant: 1e6 particles 128 -> 97 and 101 -> 90
-// us, 8e6 844 -> 684 and 767 -> 695 us, 1e5 38 -> 25 and 22.5 -> 23 us.
+// transfer launch, mask and list variant: 1e6 particles 126 -> 92 and 98 -> 85
+// us, 8e6 817 -> 654 and 724 -> 677 us, 1e5 36 -> 25 and 22 -> 23 us.
 // The FP32 passes gain nothing from it: their exponential is one instruction,
 // so the second loop costs the row-sum pass what the lists save (3.2e7
 // particles 1.40 -> 1.70 ms), and the transfer pass, with a third fewer

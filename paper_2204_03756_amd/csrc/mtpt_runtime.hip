@@ -505,7 +505,11 @@ Plan make_plan(const mtpt_params& p, bool lists)
         // The per-tile sums and counts have the room that the shapes in waves
         // need (three sums a tile, whatever the species), so that a sim's bytes
         // do not depend on the rule for few tiles; three-species sims whose
-        // shapes by that rule would need more keep the others.
+        // shapes by that rule would need more keep the others.  (With their sums
+        // in the spare pids they could take the rule's: us a step, as here / so,
+        // 1.4e5 reacting particles in Kahan FP32 69 / 63, 6.4e4 at 0.5 a unit of
+        // volume FP32W 52 / 47, but 9e4 at 0.5 FP64 52 / 61, whose tiles then
+        // suit no lists, and 2.2e5 at 0.5 Kahan 68 / 73.)
         shapes(false, false);
         room_part = align_up(static_cast<size_t>(std::max<uint32_t>(std::max(q.part_blocks, q.nttiles), 1)) * 24, 256);
         room_pair = align_up(static_cast<size_t>(std::max<uint32_t>(q.ntiles, 1)) * 4, 256);
@@ -654,10 +658,10 @@ void describe(const Plan& q, mtpt_plan_t* out)
 // A sim of which more than one particle in kListShare has no list at create, or
 // one of them has more than kListCrowd neighbours, takes the masks: a wave that
 // holds one scans its rows without a list, and a small sim's launch waits for it
-// (us a step lists / masks: 2e5 reacting particles, even 88 / 99, 0.1 % in clumps
-// of 20 89 / 97, of 40 96 / 98, a single clump of 70 118 / 103, of 100 141 / 105, a
-// fifth in clumps of 25 145 / 119; 1e6, even 227 / 274, 0.1 % in clumps of 40 240 /
-// 267, five of 100 282 / 268, a Gaussian plume 1645 / 1469).
+// (us a step lists / masks: 2e5 reacting particles, even 80 / 103, 0.1 % in clumps
+// of 20 83 / 103, of 40 102 / 105, a single clump of 70 136 / 103, of 100 155 / 109,
+// a fifth in clumps of 25 146 / 131; 1e6, even 218 / 266, 0.1 % in clumps of 40 255 /
+// 274, five of 100 283 / 271, a Gaussian plume 1904 / 1597).
 constexpr uint64_t kListShare = 1000;
 constexpr uint32_t kListCrowd = 48;
 
