@@ -530,12 +530,17 @@ Plan make_plan(const mtpt_params& p, bool lists)
         // 115, 1e6 264 / 216, 8e6 1805 / 1593; one species of 5.6 neighbours 4e5 127 /
         // 104).  A list tile is one transfer tile or two along an axis.  Of the
         // shapes that suit the mask variant about as well as the one chosen above
-        // (as few tiles, halos up to 13 % larger that leave room for particles a
-        // quarter denser than their mean), the pair with the least estimated list
-        // cost is taken, by the mask variant too, so that both leave the same
-        // partial sums.  With halos no larger than that one's the tiles of 1e6
-        // particles were halves of 10 x 5 x 5 cells instead of 9 x 6 x 6: lists 230 us
-        // instead of 216, 2e7 particles 4189 instead of 3907.  Sims that a drift
+        // (up to 30 % more tiles, halos with room for particles a quarter denser
+        // than their mean), the pair with the least estimated list cost is taken, by
+        // the mask variant too, so that both leave the same partial sums.  A
+        // workgroup's cost hardly falls with its particles (600 of about 1200 at 460
+        // of them): tiles of 9 x 5 x 5 cells, 270 particles, took 265 us a step at 1e6
+        // reacting particles of 5 neighbours, two of 12 x 5 x 3, 433, take 213 (masks
+        // 247 on both), 9 x 5 x 5 at 4e6 1027 and two of 10 x 6 x 3 809 (888, 865); walks
+        // of 5.9 neighbours at 4e6, 8 x 6 x 5 and 8 x 6 x 6 cells 870 and 784 (873, 839).
+        // Halves of up to 237 particles (1.2 standard deviations below the 256 that
+        // are summed without reading masses back): at 2e5 particles of 4.4
+        // neighbours two of 12 x 6 x 3 cells 69 us, one of 10 x 5 x 5 85.  Sims that a drift
         // gathers at the walls keep the masks, as do those whose particles are
         // found crowded at create (kListShare).
         if (q.dim == 3 && q.prec == MTPT_FP64 && !q.tensor && !q.trim_rows) {
@@ -545,43 +550,41 @@ Plan make_plan(const mtpt_params& p, bool lists)
             const double mean = rho_c / side3 * 4.18879 * q.psi * q.psi * q.psi;
             auto own_of = [&](const int* t) { return t[0] * t[1] * static_cast<double>(t[2]) * rho_c; };
             auto halo_of = [&](const int* t) { return (t[0] + 2.0) * (t[1] + 2.0) * (t[2] + 2.0) * rho_c; };
-            const double halo_max = std::min(1.13 * halo_of(q.ttile), tile_capacity(3, q.prec, q.ns) / 1.25);
+            const double halo_max = tile_capacity(3, q.prec, q.ns) / 1.25;
             const bool drift = p.vel[0] != 0.0 || p.vel[1] != 0.0 || p.vel[2] != 0.0;
+            const double most = 1.3 * q.nttiles;
             double best = 0.0;
             int tt[3] = {1, 1, 1}, lt[3] = {1, 1, 1};
             uint32_t lx = 0, ly = 0;
-            // (as many transfer tiles as chosen above at most, else 8 % or 17 %
-            // more: where those are eight cells wide, and two are beyond the limits)
-            for (double most = q.nttiles; best == 0.0 && most < 1.2 * q.nttiles; most *= 1.08)
-                for (int z = 1; z <= std::min(q.nc[2], tile_max(3, 2)); ++z)
-                    for (int y = 1; y <= std::min(q.nc[1], tile_max(3, 1)); ++y)
-                        for (int x = 1; x <= std::min(q.nc[0], tile_max(3, 0)); ++x) {
-                            const int t[3] = {x, y, z};
-                            const double sub = own_of(t);
-                            if (halo_of(t) > halo_max || count(t, &lx, &ly) > most)
+            for (int z = 1; z <= std::min(q.nc[2], tile_max(3, 2)); ++z)
+                for (int y = 1; y <= std::min(q.nc[1], tile_max(3, 1)); ++y)
+                    for (int x = 1; x <= std::min(q.nc[0], tile_max(3, 0)); ++x) {
+                        const int t[3] = {x, y, z};
+                        const double sub = own_of(t);
+                        if (halo_of(t) > halo_max || count(t, &lx, &ly) > most)
+                            continue;
+                        for (int axis = 0; axis <= kListWhole; ++axis) {
+                            int l[3] = {x, y, z};
+                            if (axis < kListWhole)
+                                l[axis] *= 2;
+                            const double own = own_of(l), halo = halo_of(l);
+                            if (axis < kListWhole && (l[axis] > tile_max(3, axis) || t[axis] >= q.nc[axis] ||
+                                                      sub + 1.2 * std::sqrt(sub) > kBlock))
                                 continue;
-                            for (int axis = 0; axis <= kListWhole; ++axis) {
-                                int l[3] = {x, y, z};
-                                if (axis < kListWhole)
-                                    l[axis] *= 2;
-                                const double own = own_of(l), halo = halo_of(l);
-                                if (axis < kListWhole && (l[axis] > tile_max(3, axis) || t[axis] >= q.nc[axis] ||
-                                                          sub + 1.5 * std::sqrt(sub) > kBlock))
-                                    continue;
-                                if (halo * 1.25 > kListCap || own + 2.0 * std::sqrt(own) > kListBlock || own < kListBlock / 2)
-                                    continue;
-                                const uint32_t nl = count(l, &lx, &ly);
-                                const double cost = nl * (64.0 * std::ceil(own / 64.0 + 0.5) + 0.1 * halo);
-                                if (nl < min_tiles)
-                                    continue;
-                                if (best == 0.0 || cost < best) {
-                                    best = cost;
-                                    q.lsplit = axis;
-                                    std::copy(t, t + 3, tt);
-                                    std::copy(l, l + 3, lt);
-                                }
+                            if (halo * 1.25 > kListCap || own + 2.0 * std::sqrt(own) > kListBlock || own < kListBlock / 2)
+                                continue;
+                            const uint32_t nl = count(l, &lx, &ly);
+                            const double cost = nl * (600.0 + 64.0 * std::ceil(own / 64.0 + 0.5) + 0.1 * halo);
+                            if (nl < min_tiles)
+                                continue;
+                            if (best == 0.0 || cost < best) {
+                                best = cost;
+                                q.lsplit = axis;
+                                std::copy(t, t + 3, tt);
+                                std::copy(l, l + 3, lt);
                             }
                         }
+                    }
             if (best > 0.0 && 1.0 + mean + 4.5 * std::sqrt(mean) <= kListMax) {
                 std::copy(tt, tt + 3, q.ttile);
                 q.nttiles = count(q.ttile, &q.ttiles_x, &q.ttiles_y);

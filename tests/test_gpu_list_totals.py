@@ -18,9 +18,9 @@ def mt():
 
 
 # (particles, box, species, axis of the two transfer tiles (None: one), particles in the first tile's cells)
-CASES = [(995, [18.3, 7.0, 18.0], 1, 0, 0), (9001, [20.8, 20.8, 20.8], 3, 0, 0), (1411, [8.8, 12.6, 22.8], 3, 0, 420),
+CASES = [(1311, [19.3, 13.9, 8.3], 1, 0, 0), (9001, [20.8, 20.8, 20.8], 3, 2, 0), (1411, [8.8, 12.6, 22.8], 3, 0, 420),
          (1303, [21.4, 11.0, 11.9], 1, 1, 0), (1267, [19.0, 5.2, 15.0], 3, 1, 0), (1155, [8.4, 16.9, 10.2], 1, 2, 0),
-         (2993, [16.2, 22.3, 18.0], 3, 0, 0), (27427, [29.2, 35.2, 35.7], 3, 0, 0), (15667, [16.6, 23.9, 43.0], 3, None, 0),
+         (1317, [19.0, 6.4, 13.9], 3, 0, 0), (13707, [32.6, 23.7, 24.7], 3, 2, 0), (5301, [18.2, 43.3, 9.7], 3, 1, 0),
          (1189, [8.8, 7.2, 23.5], 3, 2, 0), (1051, [20.4, 7.1, 10.6], 1, None, 0), (1101, [13.3, 15.8, 11.6], 3, None, 560)]
 
 
@@ -64,7 +64,7 @@ def test_sums_that_the_ordinary_place_has_no_room_for(mt, oracle, monkeypatch, p
     after every step and at the end only."""
     monkeypatch.setenv("MTPT_MIN_TILES", "1")
     rng = np.random.Generator(np.random.Philox(20230123))
-    n, hi, psi = 27427, np.array([29.2, 35.2, 35.7]), 1.1
+    n, hi, psi = 13707, np.array([32.6, 23.7, 24.7]), 1.1
     p = W.Params(dim=3, n=n, lo=[0.0] * 3, hi=list(hi), d_rw=d_rw, d_mt=psi * psi / 3.6, dt=0.1, psi=psi, seed=6,
                  n_species=3, k_react=1.0, precision=W.FP64)
     x, m = rng.random((n, 3)) * hi, rng.random((3, n))

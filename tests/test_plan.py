@@ -59,3 +59,14 @@ def test_reacting_sims_of_every_size_take_lists(n):
     plan = mtpt.mtpt_plan(_cube(n, 32e6 / 318.0 ** 3, 3, W.FP64, 0.7, 0.05))
     assert plan["lists"], plan
     assert plan["tile"][0] * plan["tile"][1] * plan["tile"][2] <= 12 * 6 * 6
+
+
+@pytest.mark.parametrize("n,neighbours,ns", [(200_003, 4.4, 3), (1_000_001, 5.0, 3), (4_000_003, 5.0, 3), (4_000_003, 5.9, 1)])
+def test_list_tiles_fill_their_workgroup(n, neighbours, ns):
+    """A workgroup of 512 threads takes about as long for half as many
+    particles: where two transfer tiles or a larger one fill it, they do."""
+    psi = 1.1
+    per_unit = neighbours / (4.18879 * psi ** 3)
+    plan = mtpt.mtpt_plan(_cube(n, per_unit, ns, W.FP64, psi * psi / 3.6, 0.1, psi=psi))
+    nc = int((n / per_unit) ** (1.0 / 3.0) / (psi * (1 + 1e-6)))
+    assert plan["lists"] and plan["tile"][0] * plan["tile"][1] * plan["tile"][2] * n / nc ** 3 >= 384, plan
